@@ -135,8 +135,16 @@ enum GemmCfg : int {
     GEMM_DMA_64x64_1W_S2 = 30,    // 1 wave, 64x64, 2 stages
     GEMM_DMA_64x64_2W_S3 = 31,    // 2 waves, 3 stages, software-pipelined
     GEMM_DMA_128x128_8W_S4 = 32,  // 8 waves, 4 stages (two in flight, one block per CU)
-    GEMM_NCFG = 33
+    GEMM_NCFG = 33,               // configurations a tuning override may name
+    // fp32 layers on bf16 matrix instructions (exact three-way operand split);
+    // channels x pixels of a block's tile, the planner's choice only
+    GEMM_SPLIT_64x128 = 33,       // 4 waves along the pixels
+    GEMM_SPLIT_64x64 = 34,        // 2 waves along the pixels x 2 K parts
+    GEMM_SPLIT_32x64 = 35,        // 2 waves along the pixels x 2 K parts
+    GEMM_SPLIT_32x32 = 36,        // 4 K parts
+    GEMM_NCFG_ALL = 37
 };
+inline bool is_split_cfg(int cfg) { return cfg >= GEMM_SPLIT_64x128 && cfg < GEMM_NCFG_ALL; }
 struct GemmCfgInfo {
     int bm, bn, kv;       // tile rows (co), columns (m); kv: 16-byte vectors of K per LDS stage
     bool skinny;
@@ -169,6 +177,14 @@ hipError_t launch_conv_gemm(int dt, int cfg, int wk, bool tapv, const ConvGemmAr
 hipError_t launch_conv_gemm_pair(int dt, int cfg, const ConvGemmArgs& a0, const ConvGemmArgs& a1,
                                  hipStream_t s);
 const char* conv_gemm_name(int dt, int cfg, int wk, bool tapv);
+
+// fp32 layers on bf16 matrix instructions (GEMM_SPLIT_*): one K split, no
+// softmax, no per-vector taps.  w3: the layer's weight planes, written by
+// launch_split_weights from the packed fp32 weights [Co][Kpad]
+// (split_weight_bytes of them, below 2 GiB); a.w stays the fp32 weights.
+size_t split_weight_bytes(int Co, int K);
+hipError_t launch_split_weights(const void* w, void* w3, int Co, int K, int Kpad, hipStream_t s);
+hipError_t launch_conv_gemm_split(int cfg, const ConvGemmArgs& a, const void* w3, hipStream_t s);
 
 // Streaming 1x1 convolution (GEMM_PW) of a 16-bit layer with C <= 32, or
 // C <= 160 with cf <= 2 (C a multiple of 8), Co % 4 == 0, stride 1, no

@@ -121,10 +121,13 @@ struct LayerRT {
     bool tapv = false, softmax = false, skinny_ok = false, pad_in = false;
     bool pw_ok = false;         // the streaming 1x1 kernel applies (GEMM_PW)
     bool stem_ok = false;       // the stem kernel applies (GEMM_STEM)
+    bool split_ok = false;      // the split fp32 kernels apply (GEMM_SPLIT_*)
     int KH = 1, KW = 1, gstride = 1, gpad = 0, K = 0, Kpad = 0;
     int cpad = 0;               // channels as the GEMM reads them (C rounded up to a vector)
     size_t w_off = 0, scale_off = 0, bias_off = 0;
     void* w = nullptr;
+    size_t w3_off = 0;          // weight planes of the split fp32 kernels, if any batch plans one
+    void* w3 = nullptr;
     float* scale = nullptr;
     float* bias = nullptr;
     int in_buf = BUF_IN, res_buf = BUF_NONE, out_buf = BUF_OUT;
@@ -188,7 +191,7 @@ namespace {
 // dtype, eligibility) so that the latency table, the benchmark and the
 // parity tests exercise the same launches.
 Plan choose_plan(int M, int Co, int K, int dt, bool skinny_ok, bool pw_ok, bool stem_ok,
-                 bool split_free, const ppipe_tuning& tune, int cus)
+                 bool split_ok, bool split_free, const ppipe_tuning& tune, int cus)
 {
     // Grid-size thresholds below are stated for the 256 CUs of a whole
     // MI355X and scale with the CUs the handle runs on (a CU share of a
@@ -305,6 +308,35 @@ Plan choose_plan(int M, int Co, int K, int dt, bool skinny_ok, bool pw_ok, bool 
     if (stem_ok && !tune.no_stem) {
         cfg = GEMM_STEM;
         wk = stem_channel_frags(Co);
+        splits = 1;
+    }
+    //  * fp32 layers with K >= 256 and more than one 32-pixel tile take the
+    //    split kernels (bf16 matrix instructions, exact operands), on the tile
+    //    that finishes first: a tile of 64x128, 64x64, 32x64 or 32x32 takes
+    //    about 0.8, 0.48, 0.32 or 0.22 us per 32 k whether its CU holds one or
+    //    two, so the estimate is that times the tiles per CU, at least one.
+    //    Measured against the fp32 kernels, in layer order: ResNet-18's 3x3
+    //    layers at batch 16 45 -> 27 (64 channels), 44 -> 35 (128), 70 -> 36 us
+    //    (256), at batch 64 140 -> 91, 140 -> 93, 156 -> 82, 227 -> 104, at batch
+    //    1 10.1 -> 8.1 (64), 13.2 -> 11 (128), 35 -> 30 (512).  Below K = 256 the
+    //    layers are bound by memory and launch (1x1 64->256 at M = 50176: 27.0
+    //    against 27.8, 128->256 at M = 3136: 6.0 against 7.2); a single tile
+    //    row is bound by the weights, which the planes make 1.5x larger.
+    //    Relative error against 64-bit sums, ResNet-18 [0, 21): 4.3e-7 to
+    //    5.4e-7 with the fp32 instruction, 2.5e-7 to 3.1e-7 split.
+    if (split_ok && tune.gemm_cfg < 0 && K >= 256 && M > 32) {
+        const int cfgs[4] = {GEMM_SPLIT_64x128, GEMM_SPLIT_64x64, GEMM_SPLIT_32x64,
+                             GEMM_SPLIT_32x32};
+        const double per[4] = {0.8, 0.48, 0.32, 0.22};
+        double best = 0.0;
+        for (int i = 0; i < 4; ++i) {
+            const double t = per[i] * std::max(1.0, (double)tiles(cfgs[i]) / (double)C);
+            if (i == 0 || t < best) {
+                best = t;
+                cfg = cfgs[i];
+            }
+        }
+        wk = 0;
         splits = 1;
     }
     // The gemm_cfg tuning override (with gemm_waves, gemm_splits) forces one
@@ -544,7 +576,8 @@ hipError_t enqueue_layer(const ppipe_partition* P, const LayerRT& l, int batch, 
             gemm_args(P, l, batch, pad ? (const void*)W.pad : x, res, y, pad, W);
         if (want(li)) {
             if (hook) hook->before(l, li, s);
-            e = launch_conv_gemm(P->dtype, p.cfg, p.wk, tapv_of(l, p), a, s);
+            e = is_split_cfg(p.cfg) ? launch_conv_gemm_split(p.cfg, a, l.w3, s)
+                                    : launch_conv_gemm(P->dtype, p.cfg, p.wk, tapv_of(l, p), a, s);
             if (hook) hook->after(l, li, s);
             if (e != hipSuccess) return e;
         }
@@ -826,6 +859,9 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
                       (x.c <= 32 || (x.c <= 160 && o.c <= 32));
             // stem kernel: an image of at most 4 channels (below one vector), <= 52 taps
             l.stem_ok = ld.op == PPIPE_OP_CONV && l.pad_in && x.c <= 4 && l.KH * l.KW <= 52;
+            // split fp32 kernels: whole 32-k chunks per tap
+            l.split_ok = dt == DT_F32 && !l.tapv && !l.pad_in && !l.softmax &&
+                         split_weight_bytes(o.c, l.K) < 2147483648u;
             if (l.tapv && l.Kpad / epv > GEMM_VTAB_MAX)
                 return fail(PPIPE_E_UNSUPPORTED, who + ": reduction length " +
                                                      std::to_string(l.K) + " with C = " +
@@ -1005,7 +1041,7 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
         for (int b = 1; b <= P->max_batch; ++b) {
             const int M = b * l.Ho * l.Wo;
             const Plan p = choose_plan(M, l.Co, l.K, dt, l.skinny_ok, l.pw_ok, l.stem_ok,
-                                       l.softmax, P->tune, P->cus);
+                                       l.split_ok, l.softmax, P->tune, P->cus);
             l.plans[b - 1] = p;
             size_t need = 0;
             if (p.splits > 1) need += (size_t)p.splits * M * l.Co;
@@ -1014,6 +1050,15 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
         }
     }
     P->ws_bytes = ws;
+    // weight planes of the layers that a split kernel runs at some batch:
+    // behind the uploaded parameters, written on the device
+    P->wbytes = P->host_blob.size();
+    for (LayerRT& l : P->L)
+        if (std::any_of(l.plans.begin(), l.plans.end(),
+                        [](const Plan& p) { return is_split_cfg(p.cfg); })) {
+            l.w3_off = align(P->wbytes);
+            P->wbytes = l.w3_off + split_weight_bytes(l.Co, l.K);
+        }
     for (const LayerRT& l : P->L)
         if (l.kind == K_GEMM)
             for (int b = 1; b <= P->max_batch; ++b)
@@ -1031,9 +1076,8 @@ int allocate(ppipe_partition* P)
 {
     hipError_t e = hipGetDevice(&P->device);
     if (e != hipSuccess) return fail(PPIPE_E_HIP, hip_msg("hipGetDevice", e));
-    e = hipMalloc(&P->wblob, P->host_blob.size());
+    e = hipMalloc(&P->wblob, P->wbytes);
     if (e != hipSuccess) return fail(PPIPE_E_NOMEM, hip_msg("hipMalloc(weights)", e));
-    P->wbytes = P->host_blob.size();
     e = hipMemcpy(P->wblob, P->host_blob.data(), P->host_blob.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return fail(PPIPE_E_HIP, hip_msg("hipMemcpy(weights)", e));
     std::vector<uint8_t>().swap(P->host_blob);
@@ -1059,6 +1103,16 @@ int allocate(ppipe_partition* P)
     }
     e = hipStreamCreateWithFlags(&P->cap_stream, hipStreamNonBlocking);
     if (e != hipSuccess) return fail(PPIPE_E_HIP, hip_msg("hipStreamCreate", e));
+    bool planes = false;
+    for (LayerRT& l : P->L) {
+        if (!l.w3_off) continue;
+        l.w3 = (uint8_t*)P->wblob + l.w3_off;
+        e = launch_split_weights(l.w, l.w3, l.Co, l.K, l.Kpad, P->cap_stream);
+        if (e != hipSuccess) return fail(PPIPE_E_HIP, hip_msg("split_weights", e));
+        planes = true;
+    }
+    if (planes && (e = hipStreamSynchronize(P->cap_stream)) != hipSuccess)
+        return fail(PPIPE_E_HIP, hip_msg("split_weights", e));
     return PPIPE_OK;
 }
 
