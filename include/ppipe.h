@@ -118,7 +118,8 @@ typedef struct {
     double param_bytes;              /* weight bytes in dtype + fp32 scale/bias, once per run */
     char kernel[96];                 /* kernel configuration chosen at the queried batch;
                                         ends in " paired=J" when the layer runs in one
-                                        launch with layer J */
+                                        launch with layer J, in " fused=I-K" when layers
+                                        I to K run in one launch */
     char name[64];                   /* the layer's name from its description */
     int32_t forced;                  /* 1 when a tuning override chose this layer's
                                         kernel at the queried batch */
@@ -158,7 +159,7 @@ typedef struct {
     int32_t no_pointwise;  /* nonzero: never plan the streaming 1x1 kernel */
     int32_t no_stem;       /* nonzero: never plan the stem kernel */
     int32_t stream_grid;   /* > 0: blocks along the pixels of the streaming 1x1 and stem kernels */
-    int32_t no_pair;       /* nonzero: never run paired layers as one launch */
+    int32_t no_pair;       /* nonzero: never run several layers as one launch */
     int32_t dw_outputs;    /* 0, or 2 / 4 outputs per thread of stride-1 depthwise layers */
 } ppipe_tuning;
 
@@ -191,8 +192,10 @@ ppipe_partition* ppipe_partition_create_on_share(const ppipe_model_desc* desc,
  * replayed, otherwise the kernels are launched directly.  A GEMM layer and
  * a later GEMM layer that read the same tensor (a residual stage's first
  * convolution and its downsample projection) go out as one launch when both
- * are planned on the same tile configuration without a K split; timed and
- * profiled runs keep one launch sequence per layer.  Concurrent runs of
+ * are planned on the same tile configuration without a K split, and so do the
+ * three layers of an inverted-residual block (1x1 expansion, depthwise, 1x1
+ * projection) of few channels; timed and profiled runs keep one launch
+ * sequence per layer.  Concurrent runs of
  * one handle on different streams race on its buffers. */
 int ppipe_partition_run(ppipe_partition* h, int32_t batch, const void* in,
                         void* out, void* stream);

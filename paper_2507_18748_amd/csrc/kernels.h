@@ -227,6 +227,24 @@ hipError_t launch_dwconv(int dt, const void* x, const void* w, const float* scal
                          hipStream_t s);
 const char* dwconv_name(int dt, int k);
 
+// Inverted-residual block in one launch (16-bit types): 1x1 expansion C -> Ce,
+// 3x3 depthwise (stride 1 or 2), 1x1 projection Ce -> Co with an optional
+// residual.  C, Ce multiples of 8, Co of 4, within the limits below.  Weights as the layers' own kernels
+// take them (we [Ce][Kpe], wd [3][3][Ce], wp [Co][Kpp]).
+struct FusedBlockArgs {
+    const void *x, *we, *wd, *wp;
+    const float *se, *be, *sd, *bd, *sp, *bp;   // folded BN of the three layers
+    const void* res;                            // [N][Ho][Wo][Co], or null
+    void* y;
+    int N, H, W, C, Ce, Co, Ho, Wo, Kpe, Kpp;
+    int stride, pad, acte, actd, actp;
+    int TH, TW, tiles_h, tiles_w;               // output tile of a block
+};
+constexpr int FUSED_MAX_C = 32, FUSED_MAX_CE = 192, FUSED_MAX_CO = 64;
+// Output tile of at most 64 pixels: the fewest tiles, then the smallest halo.
+void fused_block_tile(int Ho, int Wo, int stride, int* TH, int* TW);
+hipError_t launch_fused_block(int dt, const FusedBlockArgs& a, hipStream_t s);
+
 // k x k max pooling, NHWC; out-of-range taps never win.
 hipError_t launch_maxpool(int dt, const void* x, void* y, int N, int H, int W, int C,
                           int Ho, int Wo, int k, int stride, int pad, hipStream_t s);

@@ -105,6 +105,12 @@ struct Shape {
     int c, h, w;
 };
 
+// One launch for an inverted-residual block at one batch (on: it runs).
+struct FusePlan {
+    bool on = false;
+    int TH = 0, TW = 0, tiles_h = 0, tiles_w = 0;
+};
+
 // Scratch memory of a run: split-K partial sums followed by the fp32 logits
 // of a final FC + softmax (ws), and the channel-padded input of a stem (pad).
 struct Workspace {
@@ -135,6 +141,10 @@ struct LayerRT {
     // and may run with in one launch (-1: none); pair_lead on the earlier one
     int pair = -1;
     bool pair_lead = false;
+    // first of the three layers of an inverted-residual block, and the plan of
+    // the one launch per batch
+    bool fuse = false;
+    std::vector<FusePlan> fuse_plans;
     std::vector<Plan> plans;   // [batch - 1]
     std::string name;          // the description's layer name, or "layer<i>"
     int64_t out_bytes_b1 = 0;
@@ -393,6 +403,27 @@ Plan choose_plan(int M, int Co, int K, int dt, bool skinny_ok, bool pw_ok, bool 
     return p;
 }
 
+// Plan of an inverted-residual block as one launch: always for the shapes the
+// kernel takes, but for blocks of more than 144 expanded channels (six chunks
+// in a row) only from 48 tiles on, where the launches it replaces take longer
+// (MobileNetV2 [0, 39) with and without them: batch 1 146.9 -> 148.4 us, 3
+// 150.4 -> 150.7, 5 154.9 -> 153.1, 10 182 -> 177, 32 282 -> 251).  Blocks of
+// 64 and more input channels gain nothing (14x14 maps, 384 channels, batch 32:
+// 20.0 us as three launches, 24.9 as one), and neither does a depthwise layer
+// and its projection alone (32 channels at 112x112, batch 32: 321 -> 325 us).
+FusePlan choose_fuse(const LayerRT& dw, int batch, const ppipe_tuning& tune, int cus)
+{
+    FusePlan f;
+    if (tune.no_pair || tune.gemm_cfg >= 0 || tune.no_pointwise || tune.stream_grid ||
+        tune.dw_outputs)
+        return f;
+    fused_block_tile(dw.Ho, dw.Wo, dw.stride, &f.TH, &f.TW);
+    f.tiles_h = (dw.Ho + f.TH - 1) / f.TH;
+    f.tiles_w = (dw.Wo + f.TW - 1) / f.TW;
+    f.on = dw.C <= 144 || (int64_t)batch * f.tiles_h * f.tiles_w * 256 >= (int64_t)48 * cus;
+    return f;
+}
+
 // The per-vector-tap variant applies to the LDS-staged kernel only; a layer
 // planned on the skinny kernel has whole K steps per tap (skinny_ok).
 bool tapv_of(const LayerRT& l, const Plan& p)
@@ -622,17 +653,45 @@ hipError_t enqueue_layer(const ppipe_partition* P, const LayerRT& l, int batch, 
     }
 }
 
+// The block that starts at position i as one launch.
+hipError_t enqueue_fused(const ppipe_partition* P, size_t i, int batch, const void* in, void* out,
+                         hipStream_t s)
+{
+    const LayerRT& l = P->L[i];
+    const FusePlan& f = l.fuse_plans[batch - 1];
+    const LayerRT& d = P->L[i + 1];   // depthwise
+    const LayerRT& p = P->L[i + 2];   // projection
+    FusedBlockArgs a;
+    a.x = buf_ptr(P, l.in_buf, in, out);
+    a.we = l.w; a.se = l.scale; a.be = l.bias;
+    a.wd = d.w; a.sd = d.scale; a.bd = d.bias;
+    a.wp = p.w; a.sp = p.scale; a.bp = p.bias;
+    a.res = buf_ptr(P, p.res_buf, in, out);
+    a.y = const_cast<void*>(buf_ptr(P, p.out_buf, in, out));
+    a.N = batch; a.H = d.H; a.W = d.W; a.C = l.C; a.Ce = d.C; a.Co = p.Co;
+    a.Ho = d.Ho; a.Wo = d.Wo;
+    a.Kpe = l.Kpad; a.Kpp = p.Kpad;
+    a.stride = d.stride; a.pad = d.pad;
+    a.acte = l.act; a.actd = d.act; a.actp = p.act;
+    a.TH = f.TH; a.TW = f.TW; a.tiles_h = f.tiles_h; a.tiles_w = f.tiles_w;
+    return launch_fused_block(P->dtype, a, s);
+}
+
 // The whole range in layer order.  Without a hook (the run and capture
 // paths), paired layers whose plans allow it go out as one launch at the
-// lead's position; runs with a hook (per-layer and per-launch timing) keep
+// lead's position, and so does an inverted-residual block; runs with a hook (per-layer and per-launch timing) keep
 // one launch sequence per layer.
 hipError_t enqueue_all(const ppipe_partition* P, int batch, const void* in, void* out,
                        hipStream_t s, LaunchHook* hook, const Workspace* wsp = nullptr)
 {
     const Workspace W = wsp ? *wsp : handle_workspace(P);
-    for (const LayerRT& l : P->L) {
+    for (size_t i = 0; i < P->L.size(); ++i) {
+        const LayerRT& l = P->L[i];
         hipError_t e;
-        if (!hook && l.pair >= 0 && pair_runs(P, l.pair_lead ? l : P->L[l.pair],
+        if (!hook && l.fuse && l.fuse_plans[batch - 1].on) {
+            e = enqueue_fused(P, i, batch, in, out, s);
+            i += 2;
+        } else if (!hook && l.pair >= 0 && pair_runs(P, l.pair_lead ? l : P->L[l.pair],
                                               l.pair_lead ? P->L[l.pair] : l, batch)) {
             if (!l.pair_lead)
                 continue;   // ran with its lead
@@ -988,6 +1047,34 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
         }
     }
 
+    // ---- inverted-residual blocks ----
+    // A 1x1 expansion, a depthwise layer and a 1x1 projection in a row, 16-bit,
+    // each read by the next one only.  The launch reads the block's input until
+    // its output is written, so the input (and the residual) must not share its
+    // slot with the output.
+    std::vector<int> readers(end - begin, 0);
+    for (int i = begin; i < n; ++i)
+        for (int r : {d->layers[i].src, d->layers[i].res_src})
+            if (r >= begin && r < end) ++readers[r - begin];
+    auto plain_1x1 = [&](const LayerRT& l) {
+        return l.kind == K_GEMM && l.op == PPIPE_OP_CONV && l.KH * l.KW == 1 && l.gstride == 1 &&
+               l.gpad == 0 && !l.pad_in && !l.softmax;
+    };
+    auto feeds_next = [&](int i) {
+        return readers[i - begin] == 1 && i + 1 < end && d->layers[i + 1].src == i;
+    };
+    for (int i = begin; i + 2 < end && dt != DT_F32; ++i) {
+        LayerRT& l = P->L[i - begin];
+        const LayerRT& dw = P->L[i + 1 - begin];
+        const LayerRT& pr = P->L[i + 2 - begin];
+        if (plain_1x1(l) && l.res_src == -1 && l.C <= FUSED_MAX_C && l.pair < 0 && feeds_next(i) &&
+            dw.kind == K_DW && dw.C <= FUSED_MAX_CE && feeds_next(i + 1) && plain_1x1(pr) &&
+            pr.Co <= FUSED_MAX_CO && pr.pair < 0 && pr.res_src < i) {
+            l.fuse = true;
+            i += 2;
+        }
+    }
+
     // ---- activation buffers by liveness ----
     // A paired layer's output slot is taken at its lead's position, so that
     // it is reserved whichever order the two run in.
@@ -996,6 +1083,8 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
         const ppipe_layer_desc& ld = d->layers[i];
         for (int r : {ld.src, ld.res_src})
             if (r >= begin) last_use[r - begin] = std::max(last_use[r - begin], i);
+        if (P->L[i - begin].fuse && ld.src >= begin)
+            last_use[ld.src - begin] = std::max(last_use[ld.src - begin], i + 2);
     }
     std::vector<int> slot_busy_until;
     auto take_slot = [&](LayerRT& l, int i, int at) {
@@ -1048,6 +1137,14 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
             if (l.softmax) need += (size_t)M * l.Co;
             ws = std::max(ws, need * sizeof(float));
         }
+    }
+    for (int i = begin; i < end; ++i) {
+        LayerRT& l = P->L[i - begin];
+        if (!l.fuse) continue;
+        l.fuse_plans.resize(P->max_batch);
+        const LayerRT& dw = P->L[i + 1 - begin];
+        for (int b = 1; b <= P->max_batch; ++b)
+            l.fuse_plans[b - 1] = choose_fuse(dw, b, P->tune, P->cus);
     }
     P->ws_bytes = ws;
     // weight planes of the layers that a split kernel runs at some batch:
@@ -1876,6 +1973,9 @@ int ppipe_layer_info(const ppipe_partition* h, int32_t index, int32_t batch,
         info->forced = p.forced ? 1 : 0;
     }
     if (l.kind == K_DW && h->tune.dw_outputs) info->forced = 1;
+    for (int i = std::max(0, l.index - h->begin - 2); i <= l.index - h->begin; ++i)
+        if (h->L[i].fuse && h->L[i].fuse_plans[batch - 1].on)
+            k += " fused=" + std::to_string(h->L[i].index) + "-" + std::to_string(h->L[i + 2].index);
     std::snprintf(info->kernel, sizeof(info->kernel), "%s", k.c_str());
     return PPIPE_OK;
 }

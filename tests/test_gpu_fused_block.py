@@ -1,0 +1,76 @@
+"""Inverted-residual blocks in one launch: the bits of the separate launches at
+tile, channel-chunk and image edges, and the oracle's values."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+from gpu_util import gpu_forward, rel_inf
+from test_gpu_layers import conv, make
+
+pytestmark = pytest.mark.gpu
+
+# (C, Ce, Co, stride, pad, H, W, batch, residual, activations)
+CASES = [
+    (16, 96, 24, 2, 1, 33, 31, 2, False, ("relu6", "relu6", "none")),
+    (24, 144, 24, 1, 1, 23, 17, 3, True, ("relu6", "relu6", "none")),   # half a last chunk
+    (32, 192, 32, 1, 1, 28, 28, 4, True, ("relu6", "relu6", "none")),
+    (32, 192, 64, 2, 1, 28, 27, 13, False, ("relu", "none", "relu6")),
+    (8, 8, 4, 1, 1, 1, 1, 1, False, ("relu", "relu", "relu")),          # smallest
+    (8, 40, 20, 1, 0, 9, 65, 2, False, ("none", "none", "none")),       # no padding, a row past a tile
+    (24, 72, 36, 2, 0, 19, 18, 2, False, ("relu6", "relu", "none")),
+    (8, 24, 8, 1, 2, 5, 6, 2, False, ("relu6", "relu6", "none")),       # output larger than the input
+]
+
+
+def block(c, ce, co, s, p, res, acts):
+    return [conv("in", -1, c, c, act="none"),
+            conv("e", 0, c, ce, act=acts[0]),
+            conv("d", 1, ce, ce, 3, s, p, g=ce, act=acts[1]),
+            conv("p", 2, ce, co, act=acts[2], res=0 if res else -1),
+            conv("out", 3, co, 16, act="none")]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("c,ce,co,s,p,h,w,batch,res,acts", CASES)
+def test_fused_block(dtype, c, ce, co, s, p, h, w, batch, res, acts):
+    import oracle
+    from paper_2507_18748_amd import Partition
+    m = make((c, h, w), block(c, ce, co, s, p, res, acts))
+    P = W.model_params(m, 0, dtype)
+    x = W.partition_input((c, h, w), batch, 0, dtype, "normal")
+    outs = {}
+    # the block in the middle of a partition, and as the whole of one
+    for begin, end in ((0, 5), (1, 4)) if not res else ((0, 5), (0, 4)):
+        for tuning in (None, {"no_pair": 1}):
+            with Partition(m.layers, P, (c, h, w), begin, end, dtype, max_batch=batch,
+                           tuning=tuning) as part:
+                names = [part.layer_info(i, batch)["kernel"] for i in (1, 2, 3)]
+                assert all(("fused=1-3" in n) == (tuning is None) for n in names), names
+                a = gpu_forward(part, x)
+                if tuning is None:
+                    np.testing.assert_array_equal(gpu_forward(part, x, capture=True, reps=3), a)
+            outs[begin, end, tuning is None] = a
+        np.testing.assert_array_equal(outs[begin, end, True], outs[begin, end, False])
+    # three roundings to the storage type between input and output
+    begin, end = (1, 4) if not res else (0, 4)
+    ref = oracle.forward(m.layers, P, begin, end, x, dtype)
+    assert rel_inf(outs[begin, end, True].reshape(ref.shape), ref) <= \
+        4 * {"f16": 2.0 ** -9, "bf16": 2.0 ** -7}[dtype]
+
+
+def test_not_fused():
+    """Blocks outside the kernel's limits, or whose inner maps have another
+    reader, keep their launches."""
+    from paper_2507_18748_amd import Partition
+    for specs, h in (
+            (block(40, 96, 24, 1, 1, False, ("relu",) * 3), 9),       # C > 32
+            (block(32, 200, 24, 1, 1, False, ("relu",) * 3), 9),      # Ce > 192
+            (block(32, 96, 68, 1, 1, False, ("relu",) * 3), 9),       # Co > 64
+            (block(32, 32, 32, 1, 1, False, ("relu",) * 3)[:4] +
+             [conv("out", 3, 32, 32, act="none", res=1)], 9)):        # the expanded map read again
+        c = specs[0]["c_in"]
+        m = make((c, h, h), specs)
+        with Partition(m.layers, W.model_params(m, 0, "f16"), (c, h, h), 0, 5, "f16",
+                       max_batch=2) as part:
+            assert not any("fused" in part.layer_info(i, 2)["kernel"] for i in range(5))
