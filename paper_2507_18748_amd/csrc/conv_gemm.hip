@@ -624,12 +624,27 @@ __device__ __forceinline__ void conv_gemm_dma_body(const ConvGemmArgs& a, int bi
     }
 }
 
+// Prefetch block of a kernel with at least NW KB of dynamic LDS.
+template <int NW>
+__device__ __forceinline__ void prefetch_block(const PrefetchArgs& pf, int idx)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)dyn_smem;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    prefetch_weights(pf, idx, NW, wave, threadIdx.x & 63, lds0 + wave * 1024);
+}
+
 template <typename T, int BM, int BN, int WM, int WN, int NS, bool TAPV>
 __global__ void __launch_bounds__(WM * WN * 64)
-conv_gemm_dma(ConvGemmArgs a)
+conv_gemm_dma(ConvGemmArgs a, PrefetchArgs pf)
 {
-    const int3 g = load_args_now(a, (int)blockIdx.x, (int)gridDim.x);
-    conv_gemm_dma_body<T, BM, BN, WM, WN, NS, TAPV>(a, g.x, g.y);
+    const int bid = load_args_now(a, (int)blockIdx.x).x;
+    const int own = a.tiles_m * a.tiles_co * a.splits;
+    if (bid >= own) {
+        prefetch_block<WM * WN>(pf, bid - own);
+        return;
+    }
+    conv_gemm_dma_body<T, BM, BN, WM, WN, NS, TAPV>(a, bid, own);
 }
 
 // Warp-specialised variant of the 16-bit 128 x 128 eight-wave tile (plain
@@ -792,16 +807,21 @@ conv_gemm_ws(ConvGemmArgs a)
 // convolution and its downsample projection, which read the same input).
 struct ConvGemmPair {
     ConvGemmArgs a[2];
-    int n0;
+    int n0, n1;
+    PrefetchArgs pf;
 };
 template <typename T, int BM, int BN, int WM, int WN, int NS>
 __global__ void __launch_bounds__(WM * WN * 64)
 conv_gemm_dma_pair(ConvGemmPair p)
 {
     const int bid = (int)blockIdx.x;
+    if (bid >= p.n0 + p.n1) {
+        prefetch_block<WM * WN>(p.pf, bid - p.n0 - p.n1);
+        return;
+    }
     const int q = bid < p.n0 ? 0 : 1;   // block-uniform: one inlined body
     conv_gemm_dma_body<T, BM, BN, WM, WN, NS, false>(p.a[q], q ? bid - p.n0 : bid,
-                                                      q ? (int)gridDim.x - p.n0 : p.n0);
+                                                      q ? p.n1 : p.n0);
 }
 
 // ---- 32x32 matrix-instruction variant -------------------------------------
@@ -1162,7 +1182,7 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(ConvGemmArgs a)
 // The WK partial tiles are summed through LDS in wave order, deterministically.
 template <typename T, int FM, int FN, int WK, int DEPTH>
 __global__ void __launch_bounds__(WK * 64)
-conv_gemm_skinny(ConvGemmArgs a)
+conv_gemm_skinny(ConvGemmArgs a, PrefetchArgs pf)
 {
     constexpr int ESZ = (int)sizeof(T);
     constexpr int EPV = 16 / ESZ;
@@ -1174,8 +1194,15 @@ conv_gemm_skinny(ConvGemmArgs a)
     // wave-uniform: keeps the K-step and tap arithmetic on the scalar unit
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, r = lane & 15;
-    const int3 bg = load_args_now(a, (int)blockIdx.x, (int)gridDim.x);
-    const int3 tt = tile_of_block(a, bg.x, bg.y);
+    const int bid = load_args_now(a, (int)blockIdx.x).x;
+    const int own = a.tiles_m * a.tiles_co;
+    if (bid >= own) {
+        const uint32_t lds0 =
+            (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)&red[0][0][0];
+        prefetch_weights(pf, bid - own, WK, wave, lane, lds0 + wave * 1024);
+        return;
+    }
+    const int3 tt = tile_of_block(a, bid, own);
     const int m0 = tt.x * 16 * FN, co0 = tt.y * 16 * FM;
     const auto wsrc = make_rsrc(a.w, (uint32_t)a.Co * a.Kpad * ESZ);
     const auto xsrc = make_rsrc(a.x, (uint32_t)a.N * a.H * a.W * a.C * ESZ);
@@ -1403,7 +1430,7 @@ static hipError_t launch_lds(bool tapv, const ConvGemmArgs& a, hipStream_t s)
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int NS, bool TAPV>
-static hipError_t launch_dma_one(const ConvGemmArgs& a, hipStream_t s)
+static hipError_t launch_dma_one(const ConvGemmArgs& a, const PrefetchArgs& pf, hipStream_t s)
 {
     constexpr int bytes = gemm_lds_bytes(BM, BN, NS);
     static const hipError_t attr = hipFuncSetAttribute(
@@ -1412,13 +1439,14 @@ static hipError_t launch_dma_one(const ConvGemmArgs& a, hipStream_t s)
     if (attr != hipSuccess)
         return attr;
     PPIPE_LAUNCH((conv_gemm_dma<T, BM, BN, WM, WN, NS, TAPV>),
-                       dim3((unsigned)(a.tiles_m * a.tiles_co * a.splits)), dim3(WM * WN * 64),
-                       bytes, s, a);
+                       dim3((unsigned)(a.tiles_m * a.tiles_co * a.splits + pf.blocks)),
+                       dim3(WM * WN * 64), bytes, s, a, pf);
     return hipGetLastError();
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int NS>
-static hipError_t launch_dma_pair(const ConvGemmArgs& a0, const ConvGemmArgs& a1, hipStream_t s)
+static hipError_t launch_dma_pair(const ConvGemmArgs& a0, const ConvGemmArgs& a1,
+                                  const PrefetchArgs& pf, hipStream_t s)
 {
     constexpr int bytes = gemm_lds_bytes(BM, BN, NS);
     static const hipError_t attr = hipFuncSetAttribute(
@@ -1430,9 +1458,10 @@ static hipError_t launch_dma_pair(const ConvGemmArgs& a0, const ConvGemmArgs& a1
     p.a[0] = a0;
     p.a[1] = a1;
     p.n0 = a0.tiles_m * a0.tiles_co * a0.splits;
-    const int n1 = a1.tiles_m * a1.tiles_co * a1.splits;
-    PPIPE_LAUNCH((conv_gemm_dma_pair<T, BM, BN, WM, WN, NS>), dim3((unsigned)(p.n0 + n1)),
-                 dim3(WM * WN * 64), bytes, s, p);
+    p.n1 = a1.tiles_m * a1.tiles_co * a1.splits;
+    p.pf = pf;
+    PPIPE_LAUNCH((conv_gemm_dma_pair<T, BM, BN, WM, WN, NS>),
+                 dim3((unsigned)(p.n0 + p.n1 + pf.blocks)), dim3(WM * WN * 64), bytes, s, p);
     return hipGetLastError();
 }
 
@@ -1463,10 +1492,11 @@ static hipError_t launch_mx(bool tapv, const ConvGemmArgs& a, hipStream_t s)
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int NS>
-static hipError_t launch_dma(bool tapv, const ConvGemmArgs& a, hipStream_t s)
+static hipError_t launch_dma(bool tapv, const ConvGemmArgs& a, const PrefetchArgs& pf,
+                             hipStream_t s)
 {
-    return tapv ? launch_dma_one<T, BM, BN, WM, WN, NS, true>(a, s)
-                : launch_dma_one<T, BM, BN, WM, WN, NS, false>(a, s);
+    return tapv ? launch_dma_one<T, BM, BN, WM, WN, NS, true>(a, pf, s)
+                : launch_dma_one<T, BM, BN, WM, WN, NS, false>(a, pf, s);
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int NS, int NP>
@@ -1484,19 +1514,20 @@ static hipError_t launch_ws(const ConvGemmArgs& a, hipStream_t s)
 }
 
 template <typename T, int FM, int FN>
-static hipError_t launch_skinny(int wk, const ConvGemmArgs& a, hipStream_t s)
+static hipError_t launch_skinny(int wk, const ConvGemmArgs& a, const PrefetchArgs& pf,
+                                hipStream_t s)
 {
-    dim3 grid((unsigned)(a.tiles_m * a.tiles_co));
+    dim3 grid((unsigned)(a.tiles_m * a.tiles_co + pf.blocks));
     switch (wk) {
     case 4:
-        PPIPE_LAUNCH((conv_gemm_skinny<T, FM, FN, 4, 8>), grid, dim3(256), 0, s, a);
+        PPIPE_LAUNCH((conv_gemm_skinny<T, FM, FN, 4, 8>), grid, dim3(256), 0, s, a, pf);
         break;
     case 8:
-        PPIPE_LAUNCH((conv_gemm_skinny<T, FM, FN, 8, 8>), grid, dim3(512), 0, s, a);
+        PPIPE_LAUNCH((conv_gemm_skinny<T, FM, FN, 8, 8>), grid, dim3(512), 0, s, a, pf);
         break;
     case 16:   // 1024 threads: only the 16x16 tile fits the register file
         if constexpr (FM * FN == 1) {
-            PPIPE_LAUNCH((conv_gemm_skinny<T, FM, FN, 16, 8>), grid, dim3(1024), 0, s, a);
+            PPIPE_LAUNCH((conv_gemm_skinny<T, FM, FN, 16, 8>), grid, dim3(1024), 0, s, a, pf);
             break;
         }
         return hipErrorInvalidValue;
@@ -1508,7 +1539,7 @@ static hipError_t launch_skinny(int wk, const ConvGemmArgs& a, hipStream_t s)
 
 template <typename T>
 static hipError_t launch_cfg(int cfg, int wk, bool tapv, const ConvGemmArgs& a,
-                             hipStream_t s)
+                             const PrefetchArgs& pf, hipStream_t s)
 {
     if (gemm_cfg_info(cfg).skinny && tapv)
         return hipErrorInvalidValue;
@@ -1516,22 +1547,22 @@ static hipError_t launch_cfg(int cfg, int wk, bool tapv, const ConvGemmArgs& a,
     case GEMM_128x128:  return launch_lds<T, 128, 128, 2, 2, 8, 2>(tapv, a, s);
     case GEMM_64x64:    return launch_lds<T, 64, 64, 2, 2, 8, 2>(tapv, a, s);
     case GEMM_64x128:   return launch_lds<T, 64, 128, 2, 2, 8, 2>(tapv, a, s);
-    case GEMM_SK_32x32: return launch_skinny<T, 2, 2>(wk, a, s);
-    case GEMM_SK_32x16: return launch_skinny<T, 2, 1>(wk, a, s);
-    case GEMM_SK_16x32: return launch_skinny<T, 1, 2>(wk, a, s);
-    case GEMM_SK_16x16: return launch_skinny<T, 1, 1>(wk, a, s);
+    case GEMM_SK_32x32: return launch_skinny<T, 2, 2>(wk, a, pf, s);
+    case GEMM_SK_32x16: return launch_skinny<T, 2, 1>(wk, a, pf, s);
+    case GEMM_SK_16x32: return launch_skinny<T, 1, 2>(wk, a, pf, s);
+    case GEMM_SK_16x16: return launch_skinny<T, 1, 1>(wk, a, pf, s);
     case GEMM_128x128_8W: return launch_lds<T, 128, 128, 2, 4, 8, 2>(tapv, a, s);
     case GEMM_128x64:   return launch_lds<T, 128, 64, 2, 2, 8, 2>(tapv, a, s);
-    case GEMM_DMA_64x64_S2: return launch_dma<T, 64, 64, 2, 2, 2>(tapv, a, s);
-    case GEMM_DMA_64x64_S3: return launch_dma<T, 64, 64, 2, 2, 3>(tapv, a, s);
-    case GEMM_DMA_128x128_8W_S2: return launch_dma<T, 128, 128, 2, 4, 2>(tapv, a, s);
-    case GEMM_DMA_128x128_8W_S3: return launch_dma<T, 128, 128, 2, 4, 3>(tapv, a, s);
-    case GEMM_DMA_64x64_8W_S2: return launch_dma<T, 64, 64, 2, 4, 2>(tapv, a, s);
-    case GEMM_DMA_64x64_8W_S3: return launch_dma<T, 64, 64, 2, 4, 3>(tapv, a, s);
-    case GEMM_DMA_64x64_8W_S4: return launch_dma<T, 64, 64, 2, 4, 4>(tapv, a, s);
-    case GEMM_DMA_64x64_8W_S6: return launch_dma<T, 64, 64, 2, 4, 6>(tapv, a, s);
-    case GEMM_DMA_64x128_8W_S2: return launch_dma<T, 64, 128, 2, 4, 2>(tapv, a, s);
-    case GEMM_DMA_64x256_8W_S2: return launch_dma<T, 64, 256, 2, 4, 2>(tapv, a, s);
+    case GEMM_DMA_64x64_S2: return launch_dma<T, 64, 64, 2, 2, 2>(tapv, a, pf, s);
+    case GEMM_DMA_64x64_S3: return launch_dma<T, 64, 64, 2, 2, 3>(tapv, a, pf, s);
+    case GEMM_DMA_128x128_8W_S2: return launch_dma<T, 128, 128, 2, 4, 2>(tapv, a, pf, s);
+    case GEMM_DMA_128x128_8W_S3: return launch_dma<T, 128, 128, 2, 4, 3>(tapv, a, pf, s);
+    case GEMM_DMA_64x64_8W_S2: return launch_dma<T, 64, 64, 2, 4, 2>(tapv, a, pf, s);
+    case GEMM_DMA_64x64_8W_S3: return launch_dma<T, 64, 64, 2, 4, 3>(tapv, a, pf, s);
+    case GEMM_DMA_64x64_8W_S4: return launch_dma<T, 64, 64, 2, 4, 4>(tapv, a, pf, s);
+    case GEMM_DMA_64x64_8W_S6: return launch_dma<T, 64, 64, 2, 4, 6>(tapv, a, pf, s);
+    case GEMM_DMA_64x128_8W_S2: return launch_dma<T, 64, 128, 2, 4, 2>(tapv, a, pf, s);
+    case GEMM_DMA_64x256_8W_S2: return launch_dma<T, 64, 256, 2, 4, 2>(tapv, a, pf, s);
     case GEMM_MX_128x128_S2: return launch_mx<T, 128, 128, 2, 2, 2>(tapv, a, s);
     case GEMM_MX_128x128_S3: return launch_mx<T, 128, 128, 2, 2, 3>(tapv, a, s);
     case GEMM_MX_128x128_S4: return launch_mx<T, 128, 128, 2, 2, 4>(tapv, a, s);
@@ -1540,62 +1571,68 @@ static hipError_t launch_cfg(int cfg, int wk, bool tapv, const ConvGemmArgs& a,
     case GEMM_MX_256x128_S3: return launch_mx<T, 256, 128, 4, 2, 3>(tapv, a, s);
     case GEMM_MX_128x128_8W_S2: return launch_mx<T, 128, 128, 2, 4, 2>(tapv, a, s);
     case GEMM_MX_128x128_8W_S3: return launch_mx<T, 128, 128, 2, 4, 3>(tapv, a, s);
-    case GEMM_DMA_64x64_2W_S2: return launch_dma<T, 64, 64, 1, 2, 2>(tapv, a, s);
-    case GEMM_DMA_64x64_1W_S2: return launch_dma<T, 64, 64, 1, 1, 2>(tapv, a, s);
-    case GEMM_DMA_64x64_2W_S3: return launch_dma<T, 64, 64, 1, 2, 3>(tapv, a, s);
+    case GEMM_DMA_64x64_2W_S2: return launch_dma<T, 64, 64, 1, 2, 2>(tapv, a, pf, s);
+    case GEMM_DMA_64x64_1W_S2: return launch_dma<T, 64, 64, 1, 1, 2>(tapv, a, pf, s);
+    case GEMM_DMA_64x64_2W_S3: return launch_dma<T, 64, 64, 1, 2, 3>(tapv, a, pf, s);
     case GEMM_DMA_128x128_8W_S4:
         if constexpr (sizeof(T) == 2)
             if (!tapv && a.splits == 1 && !a.softmax && a.Co % 8 == 0)
                 return launch_ws<T, 128, 128, 2, 4, 4, 8>(a, s);
-        return launch_dma<T, 128, 128, 2, 4, 4>(tapv, a, s);
+        return launch_dma<T, 128, 128, 2, 4, 4>(tapv, a, pf, s);
     default:            return hipErrorInvalidValue;
     }
 }
 
 template <typename T>
 static hipError_t launch_pair_cfg(int cfg, const ConvGemmArgs& a0, const ConvGemmArgs& a1,
-                                  hipStream_t s)
+                                  const PrefetchArgs& pf, hipStream_t s)
 {
     switch (cfg) {
-    case GEMM_DMA_64x64_S2: return launch_dma_pair<T, 64, 64, 2, 2, 2>(a0, a1, s);
-    case GEMM_DMA_64x64_S3: return launch_dma_pair<T, 64, 64, 2, 2, 3>(a0, a1, s);
-    case GEMM_DMA_128x128_8W_S2: return launch_dma_pair<T, 128, 128, 2, 4, 2>(a0, a1, s);
-    case GEMM_DMA_128x128_8W_S3: return launch_dma_pair<T, 128, 128, 2, 4, 3>(a0, a1, s);
-    case GEMM_DMA_64x64_8W_S2: return launch_dma_pair<T, 64, 64, 2, 4, 2>(a0, a1, s);
-    case GEMM_DMA_64x64_8W_S3: return launch_dma_pair<T, 64, 64, 2, 4, 3>(a0, a1, s);
-    case GEMM_DMA_64x64_8W_S4: return launch_dma_pair<T, 64, 64, 2, 4, 4>(a0, a1, s);
-    case GEMM_DMA_64x64_8W_S6: return launch_dma_pair<T, 64, 64, 2, 4, 6>(a0, a1, s);
-    case GEMM_DMA_64x128_8W_S2: return launch_dma_pair<T, 64, 128, 2, 4, 2>(a0, a1, s);
-    case GEMM_DMA_64x256_8W_S2: return launch_dma_pair<T, 64, 256, 2, 4, 2>(a0, a1, s);
+    case GEMM_DMA_64x64_S2: return launch_dma_pair<T, 64, 64, 2, 2, 2>(a0, a1, pf, s);
+    case GEMM_DMA_64x64_S3: return launch_dma_pair<T, 64, 64, 2, 2, 3>(a0, a1, pf, s);
+    case GEMM_DMA_128x128_8W_S2: return launch_dma_pair<T, 128, 128, 2, 4, 2>(a0, a1, pf, s);
+    case GEMM_DMA_128x128_8W_S3: return launch_dma_pair<T, 128, 128, 2, 4, 3>(a0, a1, pf, s);
+    case GEMM_DMA_64x64_8W_S2: return launch_dma_pair<T, 64, 64, 2, 4, 2>(a0, a1, pf, s);
+    case GEMM_DMA_64x64_8W_S3: return launch_dma_pair<T, 64, 64, 2, 4, 3>(a0, a1, pf, s);
+    case GEMM_DMA_64x64_8W_S4: return launch_dma_pair<T, 64, 64, 2, 4, 4>(a0, a1, pf, s);
+    case GEMM_DMA_64x64_8W_S6: return launch_dma_pair<T, 64, 64, 2, 4, 6>(a0, a1, pf, s);
+    case GEMM_DMA_64x128_8W_S2: return launch_dma_pair<T, 64, 128, 2, 4, 2>(a0, a1, pf, s);
+    case GEMM_DMA_64x256_8W_S2: return launch_dma_pair<T, 64, 256, 2, 4, 2>(a0, a1, pf, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_conv_gemm_pair(int dt, int cfg, const ConvGemmArgs& a0, const ConvGemmArgs& a1,
-                                 hipStream_t s)
+                                 const PrefetchArgs& pf, hipStream_t s)
 {
     if (gemm_cfg_info(cfg).dma == 0 || a0.splits != 1 || a1.splits != 1 || a0.softmax ||
         a1.softmax)
         return hipErrorInvalidValue;
     switch (dt) {
-    case DT_F32:  return launch_pair_cfg<float>(cfg, a0, a1, s);
-    case DT_F16:  return launch_pair_cfg<_Float16>(cfg, a0, a1, s);
-    case DT_BF16: return launch_pair_cfg<__bf16>(cfg, a0, a1, s);
+    case DT_F32:  return launch_pair_cfg<float>(cfg, a0, a1, pf, s);
+    case DT_F16:  return launch_pair_cfg<_Float16>(cfg, a0, a1, pf, s);
+    case DT_BF16: return launch_pair_cfg<__bf16>(cfg, a0, a1, pf, s);
     default:      return hipErrorInvalidValue;
     }
 }
 
+bool gemm_prefetches(int cfg)
+{
+    const GemmCfgInfo c = gemm_cfg_info(cfg);
+    return c.skinny || (c.dma && c.mfma == 16);
+}
+
 hipError_t launch_conv_gemm(int dt, int cfg, int wk, bool tapv, const ConvGemmArgs& a,
-                            hipStream_t s)
+                            const PrefetchArgs& pf, hipStream_t s)
 {
     if (cfg == GEMM_PW)
         return tapv ? hipErrorInvalidValue : launch_pointwise(dt, wk, a, a.grid_blocks, s);
     if (cfg == GEMM_STEM)
         return tapv ? hipErrorInvalidValue : launch_stem(dt, wk, a, a.grid_blocks, s);
     switch (dt) {
-    case DT_F32:  return launch_cfg<float>(cfg, wk, tapv, a, s);
-    case DT_F16:  return launch_cfg<_Float16>(cfg, wk, tapv, a, s);
-    case DT_BF16: return launch_cfg<__bf16>(cfg, wk, tapv, a, s);
+    case DT_F32:  return launch_cfg<float>(cfg, wk, tapv, a, pf, s);
+    case DT_F16:  return launch_cfg<_Float16>(cfg, wk, tapv, a, pf, s);
+    case DT_BF16: return launch_cfg<__bf16>(cfg, wk, tapv, a, pf, s);
     default:      return hipErrorInvalidValue;
     }
 }

@@ -212,6 +212,21 @@ __device__ __forceinline__ void dma_wait()
 // Wait until every LDS read this wave issued has returned its data.
 __device__ __forceinline__ void lds_read_drain() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// ---- weight prefetch ------------------------------------------------------
+// A block past a launch's own tiles reads its part of the next GEMM's weights
+// through LDS-direct loads (the data lands in LDS and is dropped), which leaves
+// them in the memory-side cache.  idx: this block among the added ones, lds:
+// this wave's 1 KB of LDS.
+__device__ __forceinline__ void prefetch_weights(const PrefetchArgs& p, int idx, int waves,
+                                                 int wave, int lane, uint32_t lds)
+{
+    const auto src = make_rsrc(p.w, p.bytes);
+    for (uint32_t o = (uint32_t)(idx * waves + wave) * 1024u; o < p.bytes;
+         o += (uint32_t)(p.blocks * waves) * 1024u)
+        dma16(src, o + lane * 16u, lds);
+    dma_wait<0>();
+}
+
 // ---- prefetched single-pass epilogue (LDS-staged kernels) ----------------
 // Dynamic LDS of a staged kernel: the stage ring, or the whole fp32
 // [pixel][channel] accumulator tile (rows padded by 4 floats) when that is

@@ -67,6 +67,14 @@ struct ConvGemmArgs {
     int grid_blocks;      // pointwise kernel: cap on blocks along the pixels (0: resident set)
 };
 
+// Weights that the next GEMM launch will read, read by blocks added to a launch
+// of this one (blocks = 0: none) so that they come from the memory-side cache.
+struct PrefetchArgs {
+    const void* w = nullptr;
+    uint32_t bytes = 0;
+    int blocks = 0;            // blocks added to the grid
+};
+
 // Bring every field of the kernel arguments into scalar registers at once.
 // Left to itself the compiler loads the argument struct in several batches,
 // each waited for before the next goes out; a kernel-argument read costs
@@ -75,7 +83,7 @@ struct ConvGemmArgs {
 // the block index passes through it, so no work that uses the arguments can
 // be scheduled before it (which would split the loads again), and so does
 // the grid size (a hidden kernel argument after the struct).
-__device__ __forceinline__ int3 load_args_now(const ConvGemmArgs& a, int bid, int grid,
+__device__ __forceinline__ int3 load_args_now(const ConvGemmArgs& a, int bid, int grid = 0,
                                               int bid_y = 0)
 {
     asm volatile("" : "+s"(bid), "+s"(grid), "+s"(bid_y) : "s"(a.x), "s"(a.w), "s"(a.scale), "s"(a.bias), "s"(a.res), "s"(a.y),
@@ -168,14 +176,17 @@ constexpr int SKINNY_MAX_WAVES = 16;
 // wk: waves per block of the skinny kernel (K split), ignored by the LDS kernel.
 // tapv: the LDS kernel looks up each 16-byte K vector's (kh, kw, ci) in a
 // table (channel count a multiple of the vector width but not of the stage).
+// pf: weights to read ahead beside the launch (LDS-direct and skinny kernels;
+// ignored by the others).
 hipError_t launch_conv_gemm(int dt, int cfg, int wk, bool tapv, const ConvGemmArgs& a,
-                            hipStream_t s);
+                            const PrefetchArgs& pf, hipStream_t s);
+bool gemm_prefetches(int cfg);
 // Two layers of one DMA tile configuration, each unsplit and without a
 // softmax, in one launch (blocks of a0 first, then of a1).  The layers must
 // not depend on each other; both take plain per-tap K steps (no per-vector
 // tap table).
 hipError_t launch_conv_gemm_pair(int dt, int cfg, const ConvGemmArgs& a0, const ConvGemmArgs& a1,
-                                 hipStream_t s);
+                                 const PrefetchArgs& pf, hipStream_t s);
 const char* conv_gemm_name(int dt, int cfg, int wk, bool tapv);
 
 // fp32 layers on bf16 matrix instructions (GEMM_SPLIT_*): one K split, no
