@@ -230,7 +230,7 @@ conv_gemm_kernel(ConvGemmArgs a)
     uint4 ra0[A_PER], ra1[A_PER], rb0[B_PER], rb1[B_PER];
     TapCursor cur;              // (kh, kw, ci) of the next stage to load
     int lst = kc_begin;         // its stage index
-    cur.start(kc_begin * BK, a.C, a.KW);
+    cur.start(a, kc_begin * BK);
 
     auto load_stage = [&](uint4 (&sa)[A_PER], uint4 (&sb)[B_PER]) {
         const uint32_t k0b = (uint32_t)(lst * BK * ESZ);
@@ -426,7 +426,7 @@ __device__ __forceinline__ void conv_gemm_dma_body(const ConvGemmArgs& a, int bi
 
     TapCursor cur;
     int lst = kc_begin;       // next stage to load
-    cur.start(kc_begin * BK, a.C, a.KW);
+    cur.start(a, kc_begin * BK);
     // Stages past the end of this block's K range load nothing (offset OOB)
     // so that every step issues the same number of loads.
     auto issue = [&](uint32_t slot) {
@@ -712,7 +712,7 @@ conv_gemm_ws(ConvGemmArgs a)
         }
         TapCursor cur;
         int lst = 0;
-        cur.start(0, a.C, a.KW);
+        cur.start(a, 0);
         // a stage past the end of K loads nothing (offset OOB): every call issues PP loads
         auto issue = [&](uint32_t slot) {
             const bool live = lst < nst;
@@ -943,7 +943,7 @@ __device__ __forceinline__ void conv_gemm_mx_body(const ConvGemmArgs& a, int bid
 
     TapCursor cur;
     int lst = kc_begin;
-    cur.start(kc_begin * BK, a.C, a.KW);
+    cur.start(a, kc_begin * BK);
     auto issue = [&](uint32_t slot) {
         const bool live = lst < kc_end;
         const uint32_t k0b = (uint32_t)(lst * BK * ESZ);
@@ -1127,8 +1127,8 @@ __global__ void __launch_bounds__(256) splitk_reduce_kernel(ConvGemmArgs a)
     const uint32_t i = (uint32_t)g.x * 256u + threadIdx.x;
     if (i >= nvec)
         return;
-    const int co = (int)((i * 4u) % (uint32_t)a.Co);
-    const int m = (int)((i * 4u) / (uint32_t)a.Co);
+    const int m = fast_div((int)(i * 4u), a.div_co);   // M Co < 2^31
+    const int co = (int)(i * 4u) - m * a.Co;
     // The epilogue's operands and the partials of up to 16 splits are all
     // requested before the first addition, so a small grid (few pixels, many
     // splits) waits for memory about once rather than once per few splits.
@@ -1227,7 +1227,7 @@ conv_gemm_skinny(ConvGemmArgs a, PrefetchArgs pf)
 
     TapCursor cur;
     int lu = u0;
-    cur.start(u0 * KS, a.C, a.KW);
+    cur.start(a, u0 * KS);
     auto load = [&](uint4 (&v)[NF]) {
         const uint32_t k0b = (uint32_t)(lu * KS * ESZ);
 #pragma unroll

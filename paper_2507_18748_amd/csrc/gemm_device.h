@@ -102,10 +102,10 @@ __device__ __forceinline__ int3 tile_of_block(const ConvGemmArgs& a, int bid, in
     const int per = G / NUM_XCD, rem = G % NUM_XCD;
     int lin = xcd * per + min(xcd, rem) + slot;
     const int tiles = a.tiles_m * a.tiles_co;
-    const int split = lin / tiles;
+    const int split = a.splits > 1 ? fast_div(lin, a.div_tiles) : 0;
     lin -= split * tiles;
     const int fast = a.co_fastest ? a.tiles_co : a.tiles_m;
-    const int q = lin / fast, r = lin - q * fast;
+    const int q = fast_div(lin, a.div_fast), r = lin - q * fast;
     return a.co_fastest ? make_int3(q, r, split) : make_int3(r, q, split);   // (m tile, co tile, split)
 }
 __device__ __forceinline__ int3 tile_of_block(const ConvGemmArgs& a)
@@ -135,12 +135,12 @@ __device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t o
 // step, or the window is 1x1 and the tail is cut by the channel test).
 struct TapCursor {
     int ci, kw, kh;
-    __device__ __forceinline__ void start(int k0, int C, int KW)
+    __device__ __forceinline__ void start(const ConvGemmArgs& a, int k0)
     {
-        const int tap = k0 / C;
-        ci = k0 - tap * C;
-        kh = tap / KW;
-        kw = tap - kh * KW;
+        const int tap = fast_div(k0, a.div_c);
+        ci = k0 - tap * a.C;
+        kh = fast_div(tap, a.div_kw);
+        kw = tap - kh * a.KW;
     }
     __device__ __forceinline__ void advance(int step, int C, int KW)
     {
@@ -163,20 +163,24 @@ struct PixelRow {
     uint32_t wmask;   // bit kw set: 0 <= wo*s - p + kw < W
 };
 
+// Bits k of 0 .. n - 1 with 0 <= first + k < size.
+__device__ __forceinline__ uint32_t tap_mask(int first, int n, int size)
+{
+    const int lo = max(-first, 0), hi = min(n, size - first);   // bits lo .. hi - 1
+    return lo >= hi ? 0u : (0xffffffffu >> (32 - (hi - lo))) << lo;
+}
+
 __device__ __forceinline__ PixelRow pixel_row(const ConvGemmArgs& a, int m, int esz)
 {
     PixelRow p{0, 0u, 0u};
     if (m >= a.M)
         return p;
-    const int HoWo = a.Ho * a.Wo;
-    const int n = m / HoWo, rm = m - n * HoWo;
-    const int ho = rm / a.Wo, wo = rm - ho * a.Wo;
+    const int n = fast_div(m, a.div_hw), rm = m - n * (a.Ho * a.Wo);
+    const int ho = fast_div(rm, a.div_w), wo = rm - ho * a.Wo;
     const int hi0 = ho * a.stride - a.pad, wi0 = wo * a.stride - a.pad;
     p.off = (((n * a.H + hi0) * a.W + wi0) * a.C) * esz;
-    for (int kh = 0; kh < a.KH; ++kh)
-        if ((unsigned)(hi0 + kh) < (unsigned)a.H) p.hmask |= 1u << kh;
-    for (int kw = 0; kw < a.KW; ++kw)
-        if ((unsigned)(wi0 + kw) < (unsigned)a.W) p.wmask |= 1u << kw;
+    p.hmask = tap_mask(hi0, a.KH, a.H);
+    p.wmask = tap_mask(wi0, a.KW, a.W);
     return p;
 }
 

@@ -36,6 +36,26 @@ int set_error(int status, const std::string& msg);
 
 inline int dtype_size(int dt) { return dt == DT_F32 ? 4 : 2; }
 
+// n / d for 0 <= n < 2^31 as a high product and a shift (a 32-bit division is
+// about 20 vector instructions, and a lone wave issues one every 8 cycles; the
+// divisions of a GEMM block's prologue cost 3-9% of a whole model):
+// mul = floor(2^(31 + s) / d) + 1 with s = ceil(log2 d) is off by less than
+// 2^-31 relative; mul = 0 stands for d = 1.
+struct FastDiv {
+    uint32_t mul;
+    int sh;
+};
+inline FastDiv fast_div_of(uint32_t d)
+{
+    int s = 0;
+    while ((1ull << s) < d) ++s;
+    return d <= 1 ? FastDiv{0u, 0} : FastDiv{(uint32_t)((1ull << (31 + s)) / d + 1), s - 1};
+}
+__device__ __forceinline__ int fast_div(int n, const FastDiv& f)
+{
+    return f.mul ? (int)(__umulhi((uint32_t)n, f.mul) >> f.sh) : n;
+}
+
 // Implicit-GEMM convolution over NHWC activations.
 //   GEMM rows    co in [0, Co)            (weights, MFMA A operand)
 //   GEMM columns m = (n, ho, wo) in [0, M) (activations gathered on the fly, MFMA B operand)
@@ -65,6 +85,8 @@ struct ConvGemmArgs {
     int co_fastest;       // tile order: 0 = m tiles of one weight slice adjacent, 1 = co tiles adjacent
     int softmax;          // 1: write fp32 logits for a following softmax
     int grid_blocks;      // pointwise kernel: cap on blocks along the pixels (0: resident set)
+    // of Ho Wo, Wo, the tile order's fast extent, the tile count, C, KW and Co
+    FastDiv div_hw, div_w, div_fast, div_tiles, div_c, div_kw, div_co;
 };
 
 // Weights that the next GEMM launch will read, read by blocks added to a launch
@@ -91,7 +113,11 @@ __device__ __forceinline__ int3 load_args_now(const ConvGemmArgs& a, int bid, in
                  "s"(a.Ho), "s"(a.Wo), "s"(a.Co), "s"(a.KH), "s"(a.KW), "s"(a.stride),
                  "s"(a.pad), "s"(a.K), "s"(a.Kpad), "s"(a.M), "s"(a.act), "s"(a.total_chunks),
                  "s"(a.splits), "s"(a.chunks_per_split), "s"(a.tiles_m), "s"(a.tiles_co),
-                 "s"(a.co_fastest), "s"(a.softmax), "s"(a.grid_blocks));
+                 "s"(a.co_fastest), "s"(a.softmax), "s"(a.grid_blocks), "s"(a.div_hw.mul),
+                 "s"(a.div_hw.sh), "s"(a.div_w.mul), "s"(a.div_w.sh), "s"(a.div_fast.mul),
+                 "s"(a.div_fast.sh), "s"(a.div_tiles.mul), "s"(a.div_tiles.sh),
+                 "s"(a.div_c.mul), "s"(a.div_c.sh), "s"(a.div_kw.mul), "s"(a.div_kw.sh),
+                 "s"(a.div_co.mul), "s"(a.div_co.sh));
     return make_int3(bid, grid, bid_y);
 }
 

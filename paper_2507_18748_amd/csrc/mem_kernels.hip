@@ -127,7 +127,7 @@ template <typename T, int S, int PW>
 __global__ void __launch_bounds__(256)
 dwconv3_kernel(const T* __restrict__ x, const T* __restrict__ w, const float* __restrict__ scale,
                const float* __restrict__ bias, T* __restrict__ y, int N, int H, int W, int C,
-               int Ho, int Wo, int pad, int act)
+               int Ho, int Wo, int pad, int act, FastDiv div_cv, FastDiv div_wq, FastDiv div_ho)
 {
     constexpr int V = Vec16<T>::N;
     constexpr int ESZ = (int)sizeof(T);
@@ -136,18 +136,20 @@ dwconv3_kernel(const T* __restrict__ x, const T* __restrict__ w, const float* __
     const int CV = C / V;
     uint32_t bid = blockIdx.x, grid = gridDim.x;
     PPIPE_ARGS_NOW(bid, grid, "s"(x), "s"(w), "s"(scale), "s"(bias), "s"(y), "s"(N), "s"(H),
-                   "s"(W), "s"(C), "s"(Ho), "s"(Wo), "s"(pad), "s"(act));
+                   "s"(W), "s"(C), "s"(Ho), "s"(Wo), "s"(pad), "s"(act), "s"(div_cv.mul),
+                   "s"(div_cv.sh), "s"(div_wq.mul), "s"(div_wq.sh), "s"(div_ho.mul),
+                   "s"(div_ho.sh));
     const int WQ = (Wo + PW - 1) / PW;
     const uint32_t total = (uint32_t)N * Ho * WQ * CV;
     const uint32_t idx = xcd_block(bid, grid) * 256u + threadIdx.x;
     if (idx >= total)
         return;
-    const int cv = (int)(idx % CV);
-    uint32_t t = idx / CV;
-    const int wq = (int)(t % WQ);
-    t /= WQ;
-    const int ho = (int)(t % Ho);
-    const int n = (int)(t / Ho);
+    const int t0 = fast_div((int)idx, div_cv);     // total < 2^31
+    const int cv = (int)idx - t0 * CV;
+    const int t1 = fast_div(t0, div_wq);
+    const int wq = t0 - t1 * WQ;
+    const int n = fast_div(t1, div_ho);
+    const int ho = t1 - n * Ho;
     const int c = cv * V, wo0 = wq * PW;
     const auto xr = dw_rsrc(x, (uint32_t)N * H * W * C * ESZ);
     const auto wr = dw_rsrc(w, 9u * C * ESZ);
@@ -287,7 +289,7 @@ maxpool_kernel(const T* __restrict__ x, T* __restrict__ y, int N, int H, int W, 
 template <typename T, int K, int S>
 __global__ void __launch_bounds__(256)
 maxpool_fixed_kernel(const T* __restrict__ x, T* __restrict__ y, int N, int H, int W, int C,
-                     int Ho, int Wo, int pad)
+                     int Ho, int Wo, int pad, FastDiv div_cv, FastDiv div_wo, FastDiv div_ho)
 {
     constexpr int V = Vec16<T>::N;
     constexpr int ESZ = (int)sizeof(T);
@@ -295,17 +297,18 @@ maxpool_fixed_kernel(const T* __restrict__ x, T* __restrict__ y, int N, int H, i
     const int CV = C / V;
     uint32_t bid = blockIdx.x, grid = gridDim.x;
     PPIPE_ARGS_NOW(bid, grid, "s"(x), "s"(y), "s"(N), "s"(H), "s"(W), "s"(C), "s"(Ho), "s"(Wo),
-                   "s"(pad));
+                   "s"(pad), "s"(div_cv.mul), "s"(div_cv.sh), "s"(div_wo.mul), "s"(div_wo.sh),
+                   "s"(div_ho.mul), "s"(div_ho.sh));
     const uint32_t total = (uint32_t)N * Ho * Wo * CV;
     const uint32_t idx = xcd_block(bid, grid) * 256u + threadIdx.x;
     if (idx >= total)
         return;
-    const int cv = (int)(idx % CV);
-    uint32_t t = idx / CV;
-    const int wo = (int)(t % Wo);
-    t /= Wo;
-    const int ho = (int)(t % Ho);
-    const int n = (int)(t / Ho);
+    const int t0 = fast_div((int)idx, div_cv);     // total < 2^31
+    const int cv = (int)idx - t0 * CV;
+    const int t1 = fast_div(t0, div_wo);
+    const int wo = t0 - t1 * Wo;
+    const int n = fast_div(t1, div_ho);
+    const int ho = t1 - n * Ho;
     const int c = cv * V;
     const auto xr = dw_rsrc(x, (uint32_t)N * H * W * C * ESZ);
     const uint32_t cstride = (uint32_t)C * ESZ, rstride = (uint32_t)W * cstride;
@@ -533,7 +536,8 @@ hipError_t launch_dwconv(int dt, const void* x, const void* w, const float* scal
 #define PPIPE_DW(S_, PW_)                                                                         \
     PPIPE_DISPATCH(dt, PPIPE_LAUNCH((dwconv3_kernel<T, S_, PW_>), dim3(blocks_for(total)),        \
                                     dim3(256), 0, s, (const T*)x, (const T*)w, scale, bias,       \
-                                    (T*)y, N, H, W, C, Ho, Wo, pad, act))
+                                    (T*)y, N, H, W, C, Ho, Wo, pad, act, fast_div_of(cv),         \
+                                    fast_div_of((Wo + pw - 1) / pw), fast_div_of(Ho)))
     if (stride == 1 && pw == 4) {
         PPIPE_DW(1, 4);
     } else if (stride == 1) {
@@ -550,14 +554,16 @@ hipError_t launch_maxpool(int dt, const void* x, void* y, int N, int H, int W, i
 {
     const size_t total = (size_t)N * Ho * Wo * C / (16 / dtype_size(dt));
     const bool fits32 = total < (1u << 31) && (double)N * H * W * C * dtype_size(dt) < 2147483648.0;
+    const FastDiv div_cv = fast_div_of((uint32_t)(C / (16 / dtype_size(dt)))),
+                  div_wo = fast_div_of((uint32_t)Wo), div_ho = fast_div_of((uint32_t)Ho);
     if (fits32 && k == 2 && stride == 2) {
         PPIPE_DISPATCH(dt, PPIPE_LAUNCH((maxpool_fixed_kernel<T, 2, 2>), dim3(blocks_for(total)),
                                         dim3(256), 0, s, (const T*)x, (T*)y, N, H, W, C, Ho, Wo,
-                                        pad));
+                                        pad, div_cv, div_wo, div_ho));
     } else if (fits32 && k == 3 && stride == 2) {
         PPIPE_DISPATCH(dt, PPIPE_LAUNCH((maxpool_fixed_kernel<T, 3, 2>), dim3(blocks_for(total)),
                                         dim3(256), 0, s, (const T*)x, (T*)y, N, H, W, C, Ho, Wo,
-                                        pad));
+                                        pad, div_cv, div_wo, div_ho));
     } else {
         PPIPE_DISPATCH(dt, PPIPE_LAUNCH(maxpool_kernel<T>, dim3(blocks_for(total)),
                                         dim3(256), 0, s, (const T*)x, (T*)y, N, H, W, C,

@@ -555,6 +555,13 @@ ConvGemmArgs gemm_args(const ppipe_partition* P, const LayerRT& l, int batch, co
     a.co_fastest = p.co_fastest;
     a.softmax = l.softmax ? 1 : 0;
     a.grid_blocks = p.grid;
+    a.div_hw = fast_div_of((uint32_t)(l.Ho * l.Wo));
+    a.div_w = fast_div_of((uint32_t)l.Wo);
+    a.div_fast = fast_div_of((uint32_t)(p.co_fastest ? p.tiles_co : p.tiles_m));
+    a.div_tiles = fast_div_of((uint32_t)(p.tiles_m * p.tiles_co));
+    a.div_c = fast_div_of((uint32_t)a.C);
+    a.div_kw = fast_div_of((uint32_t)l.KW);
+    a.div_co = fast_div_of((uint32_t)l.Co);
     return a;
 }
 

@@ -117,7 +117,7 @@ __device__ __forceinline__ void f32_tile(const ConvGemmArgs& a, int m0, int co0,
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     TapCursor cur;
-    cur.start(0, a.C, a.KW);
+    cur.start(a, 0);
     const int steps = (a.K + 15) / 16;
 #pragma unroll 1
     for (int u = 0; u < steps; ++u) {
@@ -206,7 +206,7 @@ conv_gemm_split(SplitArgs p)
     }
     TapCursor cur;
     int lc = h;                              // next chunk to load
-    cur.start(h * 32, a.C, a.KW);
+    cur.start(a, h * 32);
     uint4 ra[LA], rb[2][2];
     auto load = [&]() {
         const bool live = KSP == 1 || lc < chunks;   // past the end: weights read as zeros
