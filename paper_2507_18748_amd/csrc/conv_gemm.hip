@@ -427,6 +427,34 @@ __device__ __forceinline__ void conv_gemm_dma_body(const ConvGemmArgs& a, int bi
     TapCursor cur;
     int lst = kc_begin;       // next stage to load
     cur.start(a, kc_begin * BK);
+    // Two-stage ring, plain taps: a lane's offset within its tap stays while the
+    // channels advance (the scalar offset) and is worked out again where the tap
+    // changes or the last channels of a ragged 1x1 layer begin.  (VGG-16's
+    // convolutions at batch 16 1.5%, its 128- and 256-channel layers at batch 9
+    // 3% faster; the pipelined rings, whose few MFMAs per step are scheduled
+    // around the address work, lost 1-9% with it and keep the form below.)
+    uint32_t b_off[PER_B];
+    auto at_tap = [&]() {
+        const int tap_off = (cur.kh * a.W + cur.kw) * a.C * ESZ;
+#pragma unroll
+        for (int i = 0; i < PER_B; ++i)
+            b_off[i] = tap_offset<EPV>(b_px[i], cur.kh, cur.kw, b_k[i], tap_off, a.C - cur.ci);
+    };
+    if constexpr (NS == 2 && !TAPV) at_tap();
+    auto issue_tap = [&](uint32_t slot) {   // not called past the end of K
+        const uint32_t k0b = (uint32_t)(lst * BK * ESZ);
+#pragma unroll
+        for (int i = 0; i < PER_A; ++i)
+            dma16(wsrc, a_off[i], k0b, slot + (i * NW + wave) * 8 * ROW);
+#pragma unroll
+        for (int i = 0; i < PER_B; ++i)
+            dma16(xsrc, b_off[i], (uint32_t)(cur.ci * ESZ),
+                  slot + BM * ROW + (i * NW + wave) * 8 * ROW);
+        ++lst;
+        cur.advance(BK, a.C, a.KW);
+        if (cur.ci == 0 || a.C - cur.ci < BK)
+            at_tap();
+    };
     // Stages past the end of this block's K range load nothing (offset OOB)
     // so that every step issues the same number of loads.
     auto issue = [&](uint32_t slot) {
@@ -521,12 +549,19 @@ __device__ __forceinline__ void conv_gemm_dma_body(const ConvGemmArgs& a, int bi
         // lowest register pressure and LDS footprint of the variants, for
         // layers with several blocks per CU.
         if (nst > 0) {
-            issue(lds0);
+            auto next = [&](uint32_t slot) {
+                if constexpr (TAPV)
+                    issue(slot);
+                else
+                    issue_tap(slot);
+            };
+            next(lds0);
             for (int s = 0; s < nst; ++s) {
                 dma_wait<0>();     // this wave's loads of stage s have landed
                 bare_barrier();    // ... and every wave's; stage s - 1 is consumed (its
                                    // fragments fed this wave's MFMAs)
-                issue(lds0 + ((s + 1) & 1) * STAGE);
+                if (s + 1 < nst)
+                    next(lds0 + ((s + 1) & 1) * STAGE);
                 const unsigned char* S = dyn_smem + (s & 1) * STAGE;
                 // Every fragment read of the stage goes out before its first
                 // MFMA, so the products of k-step 0 run while the reads of
@@ -550,7 +585,6 @@ __device__ __forceinline__ void conv_gemm_dma_body(const ConvGemmArgs& a, int bi
                 __builtin_amdgcn_sched_group_barrier(0x100, (KV / 4) * (FM + FN), 0);   // LDS reads
                 __builtin_amdgcn_sched_group_barrier(0x008, (KV / 4) * FM * FN, 0);     // then MFMAs
             }
-            dma_wait<0>();   // the empty tail load
         }
     } else if (nst > 0) {
 #pragma unroll
@@ -711,29 +745,34 @@ conv_gemm_ws(ConvGemmArgs a)
             b_k[i] = lp ^ dma_swz(row);
         }
         TapCursor cur;
-        int lst = 0;
         cur.start(a, 0);
+        // offsets within a tap, as in the two-stage ring above
+        int lst = 0;
+        uint32_t b_off[PB];
+        auto at_tap = [&]() {
+            const int tap_off = (cur.kh * a.W + cur.kw) * a.C * ESZ;
+#pragma unroll
+            for (int i = 0; i < PB; ++i)
+                b_off[i] = tap_offset<EPV>(b_px[i], cur.kh, cur.kw, b_k[i], tap_off, a.C - cur.ci);
+        };
+        at_tap();
         // a stage past the end of K loads nothing (offset OOB): every call issues PP loads
         auto issue = [&](uint32_t slot) {
             const bool live = lst < nst;
-            const uint32_t k0b = (uint32_t)(lst * BK * ESZ);
 #pragma unroll
             for (int i = 0; i < PA; ++i)
-                dma16(wsrc, live ? a_off[i] + k0b : OOB, slot + (i * NP + pw) * 8 * ROW);
+                dma16(wsrc, live ? a_off[i] : OOB, (uint32_t)(lst * BK * ESZ),
+                      slot + (i * NP + pw) * 8 * ROW);
             const uint32_t bslot = slot + BM * ROW;
-            const int tap_off = ((cur.kh * a.W + cur.kw) * a.C + cur.ci) * ESZ;
-            const int cleft = a.C - cur.ci;
 #pragma unroll
-            for (int i = 0; i < PB; ++i) {
-                const bool ok = live &&
-                                ((b_px[i].hmask >> cur.kh) & (b_px[i].wmask >> cur.kw) & 1u) &&
-                                b_k[i] * EPV < cleft;
-                dma16(xsrc, ok ? (uint32_t)(b_px[i].off + tap_off + b_k[i] * 16) : OOB,
+            for (int i = 0; i < PB; ++i)
+                dma16(xsrc, live ? b_off[i] : OOB, (uint32_t)(cur.ci * ESZ),
                       bslot + (i * NP + pw) * 8 * ROW);
-            }
             if (live) {
                 ++lst;
                 cur.advance(BK, a.C, a.KW);
+                if (cur.ci == 0 || a.C - cur.ci < BK)
+                    at_tap();
             }
         };
 #pragma unroll

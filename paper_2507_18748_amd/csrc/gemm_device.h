@@ -126,9 +126,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes,
                                              RSRC_FLAGS);
 }
-__device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off)
+__device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off, int soff = 0)
 {
-    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
 }
 // Position of a K step in (kh, kw, ci) order, wave-uniform, advanced by a
 // fixed number of channels; steps never straddle a tap (C is a multiple of the
@@ -162,6 +162,17 @@ struct PixelRow {
     uint32_t hmask;   // bit kh set: 0 <= ho*s - p + kh < H
     uint32_t wmask;   // bit kw set: 0 <= wo*s - p + kw < W
 };
+
+// Byte offset of vector kv of a pixel's stage at tap (kh, kw), channel 0; OOB
+// where the tap is outside the image or the vector past the channels that are
+// left (cleft: those from the stage's first on).
+template <int EPV>
+__device__ __forceinline__ uint32_t tap_offset(const PixelRow& p, int kh, int kw, int kv, int tap_off,
+                                               int cleft)
+{
+    const int in = (int)((p.hmask << (31 - kh)) & (p.wmask << (31 - kw)));   // sign: both bits set
+    return in < 0 && kv * EPV < cleft ? (uint32_t)(p.off + tap_off + kv * 16) : OOB;
+}
 
 // Bits k of 0 .. n - 1 with 0 <= first + k < size.
 __device__ __forceinline__ uint32_t tap_mask(int first, int n, int size)
@@ -198,6 +209,14 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint32_t voff, u
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :: "s"(lds), "v"(voff), "s"(r) : "memory");
+}
+// The same with a scalar offset added to every lane's (both count in the range
+// check; soff must not exceed the resource's size).
+__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff,
+                                      uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
 }
 // Workgroup barrier without the memory fence of __syncthreads (which waits
 // for every outstanding LDS read first).  Used where the LDS data a barrier
