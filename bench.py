@@ -243,12 +243,12 @@ def write_table_json(path, out):
 def source_digest():
     """sha256 over the sources that define the GEMM kernel whose HBM counters
     are recorded and the planner that configures it (conv_gemm.hip,
-    kernels.h, runtime.hip): a change to any of them invalidates counters
-    taken before it."""
+    gemm_device.h, kernels.h, runtime.hip): a change to any of them
+    invalidates counters taken before it."""
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2507_18748_amd", "csrc")
-    for f in ("conv_gemm.hip", "kernels.h", "runtime.hip"):
+    for f in ("conv_gemm.hip", "gemm_device.h", "kernels.h", "runtime.hip"):
         with open(os.path.join(csrc, f), "rb") as fh:
             h.update(f.encode() + b"\0" + fh.read())
     return h.hexdigest()
@@ -319,7 +319,7 @@ def traffic_record(args):
                    "configuration, mean over every dispatch of the profiled command; scaled by "
                    "a plain device copy's counters (reads x fetch_scale, writes x write_scale); "
                    "bench.py reports traffic only while source_sha256 matches conv_gemm.hip, "
-                   "kernels.h and runtime.hip"}
+                   "gemm_device.h, kernels.h and runtime.hip"}
     with open(args.traffic_record, "w") as f:
         json.dump(out, f, indent=1)
     print(json.dumps(out))

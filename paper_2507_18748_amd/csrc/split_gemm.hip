@@ -23,6 +23,9 @@
 // channels x 32 pixels, so that its split (56 vector instructions per 32 k)
 // fits beside its 12 FM matrix instructions.
 //
+// Planes below the smallest normal bf16 may be flushed: an operand is exact
+// from 2^-102 on, below that it is off by less than 2^-125.
+//
 // Infinities, NaN, and magnitudes that round to an infinite bf16 leave a
 // non-finite sum (inf - inf in the split), never a finite wrong one.  A block
 // that finds one recomputes its tile with the fp32 instruction from the fp32
