@@ -221,7 +221,12 @@ const char* conv_gemm_name(int dt, int cfg, int wk, bool tapv);
 // (split_weight_bytes of them, below 2 GiB); a.w stays the fp32 weights.
 size_t split_weight_bytes(int Co, int K);
 hipError_t launch_split_weights(const void* w, void* w3, int Co, int K, int Kpad, hipStream_t s);
-hipError_t launch_conv_gemm_split(int cfg, const ConvGemmArgs& a, const void* w3, hipStream_t s);
+// tiny [Co]: sums below it make a block check its activations for values that the
+// split cannot hold; split_tiny fills it from the packed weights on the host and
+// returns its largest entry.
+float split_tiny(const float* w, int K, float* tiny, int Co, int Kpad);
+hipError_t launch_conv_gemm_split(int cfg, const ConvGemmArgs& a, const void* w3,
+                                  const float* tiny, float tiny_max, hipStream_t s);
 
 // Streaming 1x1 convolution (GEMM_PW) of a 16-bit layer with C <= 32, or
 // C <= 160 with cf <= 2 (C a multiple of 8), Co % 4 == 0, stride 1, no

@@ -134,6 +134,9 @@ struct LayerRT {
     void* w = nullptr;
     size_t w3_off = 0;          // weight planes of the split fp32 kernels, if any batch plans one
     void* w3 = nullptr;
+    size_t tiny_off = 0;        // their per-channel bounds of sums to check, and the largest
+    const float* tiny = nullptr;
+    float tiny_max = 0.0f;
     float* scale = nullptr;
     float* bias = nullptr;
     int in_buf = BUF_IN, res_buf = BUF_NONE, out_buf = BUF_OUT;
@@ -651,7 +654,7 @@ hipError_t enqueue_layer(const ppipe_partition* P, const LayerRT& l, int batch, 
                                    p.tiles_m * p.tiles_co * p.splits);
             if (hook) hook->before(l, li, s);
             e = is_split_cfg(p.cfg)
-                    ? launch_conv_gemm_split(p.cfg, a, l.w3, s)
+                    ? launch_conv_gemm_split(p.cfg, a, l.w3, l.tiny, l.tiny_max, s)
                     : launch_conv_gemm(P->dtype, p.cfg, p.wk, tapv_of(l, p), a, pf, s);
             if (hook) hook->after(l, li, s);
             if (e != hipSuccess) return e;
@@ -1013,6 +1016,9 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
         }
         l.scale_off = total; total = align(total + (size_t)l.Co * 4);
         l.bias_off = total; total = align(total + (size_t)l.Co * 4);
+        if (l.split_ok) {
+            l.tiny_off = total; total = align(total + (size_t)l.Co * 4);
+        }
     }
     std::vector<uint8_t> blob(std::max<size_t>(total, 256), 0);
     for (LayerRT& l : P->L) {
@@ -1193,12 +1199,15 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
             l.fuse_plans[b - 1] = choose_fuse(dw, b, P->tune, P->cus);
     }
     P->ws_bytes = ws;
-    // weight planes of the layers that a split kernel runs at some batch:
-    // behind the uploaded parameters, written on the device
+    // layers that a split kernel runs at some batch: the bounds of their sums,
+    // and room behind the uploaded parameters for their weight planes, which
+    // are written on the device
     P->wbytes = P->host_blob.size();
     for (LayerRT& l : P->L)
         if (std::any_of(l.plans.begin(), l.plans.end(),
                         [](const Plan& p) { return is_split_cfg(p.cfg); })) {
+            l.tiny_max = split_tiny((const float*)&P->host_blob[l.w_off], l.K,
+                                    (float*)&P->host_blob[l.tiny_off], l.Co, l.Kpad);
             l.w3_off = align(P->wbytes);
             P->wbytes = l.w3_off + split_weight_bytes(l.Co, l.K);
         }
@@ -1250,6 +1259,7 @@ int allocate(ppipe_partition* P)
     for (LayerRT& l : P->L) {
         if (!l.w3_off) continue;
         l.w3 = (uint8_t*)P->wblob + l.w3_off;
+        l.tiny = (const float*)((uint8_t*)P->wblob + l.tiny_off);
         e = launch_split_weights(l.w, l.w3, l.Co, l.K, l.Kpad, P->cap_stream);
         if (e != hipSuccess) return fail(PPIPE_E_HIP, hip_msg("split_weights", e));
         planes = true;

@@ -23,14 +23,28 @@
 // channels x 32 pixels, so that its split (56 vector instructions per 32 k)
 // fits beside its 12 FM matrix instructions.
 //
-// Planes below the smallest normal bf16 may be flushed: an operand is exact
-// from 2^-102 on, below that it is off by less than 2^-125.
+// Planes below the smallest normal bf16 (2^-126) are flushed, which an operand
+// below 2^-102 would lose bits to.  Weights are therefore split after a
+// multiplication by 2^24 (every fp32 value is a multiple of 2^-149, so every
+// scaled plane is normal or zero) that the sums carry and the tile's end takes
+// out.  Doing the same to the activations costs 3.6% (two more vector
+// instructions per pair), so they stay as they are: flushes change a sum by
+// less than 2^-124 of the filter's magnitude, which only a tiny sum can show.
+// A block with a sum below 2^-98 of it (`tiny`, zero sums among them) looks its
+// activations over, and one that finds a nonzero one below 2^-102 takes the
+// fp32 path of the next paragraph.  (Checking the sums takes 0.1 to 0.2 us of a
+// tile; maps of zeros, where every block looks, take 1.4 times as long.)
 //
-// Infinities, NaN, and magnitudes that round to an infinite bf16 leave a
-// non-finite sum (inf - inf in the split), never a finite wrong one.  A block
-// that finds one recomputes its tile with the fp32 instruction from the fp32
-// weights, so such inputs give what the fp32 kernels give.
+// Infinities, NaN, and magnitudes that round to an infinite bf16 (scaled
+// weights or sums among them, from 2^104 on) leave a non-finite sum (inf - inf
+// in the split), never a finite wrong one.  A block that finds one recomputes
+// its tile with the fp32 instruction from the fp32 weights, so such inputs give
+// what the fp32 kernels give.
 #include "gemm_device.h"
+
+#include <algorithm>
+#include <cmath>
+#include <cstring>
 
 namespace ppipe {
 
@@ -39,7 +53,11 @@ namespace {
 struct SplitArgs {
     ConvGemmArgs a;
     const void* w3;    // weight planes in fragment order
+    const float* tiny; // [Co]: scaled sums below it may have lost bits of tiny activations
+    float tiny_max;    // the largest of them
 };
+constexpr float SPLIT_W_SCALE = 0x1p24f, SPLIT_UNSCALE = 0x1p-24f;
+constexpr uint32_t SPLIT_X_MIN = (127u - 102u) << 23;   // 2^-102: every plane is normal
 
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -79,6 +97,12 @@ __device__ __forceinline__ void split8(const uint4& lo, const uint4& hi, uint4 (
     for (int q = 0; q < 3; ++q) p[q] = make_uint4(o[q][0], o[q][1], o[q][2], o[q][3]);
 }
 
+__device__ __forceinline__ uint4 scaled(const float4& v)
+{
+    return make_uint4(__float_as_uint(v.x * SPLIT_W_SCALE), __float_as_uint(v.y * SPLIT_W_SCALE),
+                      __float_as_uint(v.z * SPLIT_W_SCALE), __float_as_uint(v.w * SPLIT_W_SCALE));
+}
+
 // One thread per (16-channel group, 32-k chunk, lane).
 __global__ void __launch_bounds__(256)
 split_weights_kernel(const float* __restrict__ w, uint4* __restrict__ w3, int Co, int Kpad,
@@ -94,8 +118,8 @@ split_weights_kernel(const float* __restrict__ w, uint4* __restrict__ w3, int Co
     uint4 lo = make_uint4(0u, 0u, 0u, 0u), hi = lo;
     if (row < Co) {   // Kpad is a multiple of 64: whole vectors
         const float* src = w + (size_t)row * Kpad + k;
-        lo = *(const uint4*)src;
-        hi = *(const uint4*)(src + 16);
+        lo = scaled(*(const float4*)src);
+        hi = scaled(*(const float4*)(src + 16));
     }
     uint4 p[3];
     split8(lo, hi, p);
@@ -174,7 +198,7 @@ conv_gemm_split(SplitArgs p)
     static_assert(FM * 3 % WN == 0, "whole weight fragments per wave");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
-    asm volatile("" ::"s"(p.w3));
+    asm volatile("" ::"s"(p.w3), "s"(p.tiny), "s"(p.tiny_max));
     const int3 bg = load_args_now(a, (int)blockIdx.x, (int)gridDim.x);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -347,23 +371,74 @@ conv_gemm_split(SplitArgs p)
                 for (int j = 0; j < 2; ++j) acc[i][j] += *at(i, j);
         }
     }
-    float mag = 0.0f;   // NaN and infinities both fail the comparison below
+    // largest and least magnitude (NaN propagates: v_maximum3, v_minimum3)
+    float most = 0.0f;
+    bool small = false;
+    bool in_m[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) in_m[j] = m0 + wn * 32 + j * 16 + (lane & 15) < a.M;
     if (h == 0) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < 2; ++j) {
+                float least = INFINITY;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) mag += acc[i][j][q] * 0.0f;
+                for (int q = 0; q < 4; ++q) {
+                    const float v = fabsf(acc[i][j][q]);
+                    most = __builtin_elementwise_maximum(most, v);
+                    least = __builtin_elementwise_minimum(least, v);
+                }
+                // the tile's padding does not count
+                small |= least < p.tiny_max && in_m[j] && co0 + i * 16 + 4 * (lane >> 4) < a.Co;
+            }
     }
-    const int bad = __syncthreads_or(mag == 0.0f ? 0 : 1);
-    if (bad && h == 0)
-        f32_tile<FM>(a, m0 + wn * 32, co0, lane, acc);
+    const bool odd = !(most < INFINITY);
+    bool f32 = false;     // the tile takes the fp32 instruction
+    if (__syncthreads_or(odd || small)) {
+        f32 = __syncthreads_or(odd);
+        // again by each channel's own bound: filters of zeros have sums of zero
+        small = false;
+        if (h == 0) {
+            const auto tsrc = make_rsrc(p.tiny, (uint32_t)a.Co * 4);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+                const int co = co0 + i * 16 + 4 * (lane >> 4);
+                const floatx4 t = __builtin_bit_cast(
+                    floatx4, buf_load16(tsrc, co < a.Co ? (uint32_t)co * 4 : OOB));
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) small |= fabsf(acc[i][j][q]) < t[q] && in_m[j];
+            }
+        }
+        if (__syncthreads_or(small) && !f32) {
+            cur.start(a, h * 32);
+            lc = h;
+            bool lossy = false;
+#pragma unroll 1
+            for (int q = 0; q < nst; ++q) {
+                load();
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const uint32_t e[4] = {rb[j][k].x, rb[j][k].y, rb[j][k].z, rb[j][k].w};
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            lossy |= (e[v] & 0x7fffffffu) - 1u < SPLIT_X_MIN - 1u;
+                    }
+            }
+            f32 = __syncthreads_or(lossy);
+        }
+    }
     if (h == 0) {
+        if (f32) f32_tile<FM>(a, m0 + wn * 32, co0, lane, acc);
+        const float unscale = f32 ? 1.0f : SPLIT_UNSCALE;
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) *at(i, j) = acc[i][j];
+            for (int j = 0; j < 2; ++j) *at(i, j) = acc[i][j] * unscale;
     }
     __syncthreads();
     epre.template finish<LROW>(a, ept, m0, co0, tid);
@@ -401,9 +476,29 @@ hipError_t launch_split_weights(const void* w, void* w3, int Co, int K, int Kpad
     return hipGetLastError();
 }
 
-hipError_t launch_conv_gemm_split(int cfg, const ConvGemmArgs& a, const void* w3, hipStream_t s)
+float split_tiny(const float* w, int K, float* tiny, int Co, int Kpad)
 {
-    const SplitArgs p{a, w3};
+    float top = 0.0f;
+    for (int co = 0; co < Co; ++co) {
+        uint32_t m = 0;   // bit patterns order as the magnitudes do
+        for (int k = 0; k < Kpad; ++k) {
+            uint32_t u;
+            std::memcpy(&u, w + (size_t)co * Kpad + k, 4);
+            m = std::max(m, u & 0x7fffffffu);
+        }
+        float w_max;
+        std::memcpy(&w_max, &m, 4);
+        const double t = 0x1p-74 * K * (double)w_max;   // 2^-98 of at least the sum of |w|, scaled
+        tiny[co] = std::isfinite(t) ? (float)t : INFINITY;
+        top = std::max(top, tiny[co]);
+    }
+    return top;
+}
+
+hipError_t launch_conv_gemm_split(int cfg, const ConvGemmArgs& a, const void* w3,
+                                  const float* tiny, float tiny_max, hipStream_t s)
+{
+    const SplitArgs p{a, w3, tiny, tiny_max};
     switch (cfg) {
     case GEMM_SPLIT_64x128: return launch_one<4, 4, 1>(p, s);
     case GEMM_SPLIT_64x64:  return launch_one<4, 2, 2>(p, s);

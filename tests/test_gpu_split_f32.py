@@ -93,3 +93,60 @@ def test_split_static_scratch_and_graph():
         np.testing.assert_array_equal(gpu_forward(part, x, capture=True, reps=3), a)
     ref = oracle.forward(m.layers, W.model_params(m, 0, "f32"), 0, 1, x, "f32")
     assert rel_inf(a, ref) <= LAYER_TOL["f32"]
+
+
+def product64(x, w):
+    """1x1 convolution and the sum of its terms' magnitudes, in 64 bits."""
+    w = w[:, :, 0, 0].astype(np.float64)
+    x = x.astype(np.float64)
+    n, c, h, wd = x.shape
+    flat = x.transpose(1, 0, 2, 3).reshape(c, -1)
+    y, mag = w @ flat, np.abs(w) @ np.abs(flat)
+    shape = (w.shape[0], n, h, wd)
+    return [a.reshape(shape).transpose(1, 0, 2, 3) for a in (y, mag)]
+
+
+def run_1x1(x, w):
+    from paper_2507_18748_amd import Partition
+    c, h, wd = x.shape[1:]
+    m = make((c, h, wd), [conv("c", -1, c, w.shape[0], act="none", bn=False)])
+    with Partition(m.layers, {0: {"weight": w}}, (c, h, wd), 0, 1, "f32",
+                   max_batch=x.shape[0]) as part:
+        assert part.layer_info(0, x.shape[0])["kernel"].startswith("conv_gemm_split<f32")
+        return gpu_forward(part, x)
+
+
+def split_operands(c, co, h, batch, ex=0, ew=0, seed=0):
+    rng = np.random.default_rng(seed)
+    x = np.ldexp(np.maximum(rng.standard_normal((batch, c, h, h)), 0), ex).astype(np.float32)
+    w = np.ldexp(rng.standard_normal((co, c, 1, 1)), ew).astype(np.float32)
+    return x, w
+
+
+# K roundings of 2^-24 each to the sum of the terms' magnitudes bound any order
+# of fp32 sums; K = 256 and random signs leave a few of them
+SUM_TOL = 8 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("ex,ew", [(-102, 100), (-110, 100), (-118, 100), (-126, 100), (-130, 110),
+                                   (-140, 110), (100, -102), (100, -110), (100, -126), (100, -140)])
+@pytest.mark.parametrize("c,co,h,batch", [(256, 68, 9, 1), (288, 132, 33, 9)])
+def test_split_tiny_operands(c, co, h, batch, ex, ew):
+    """Operands down to the subnormals keep every bit: as accurate as others."""
+    x, w = split_operands(c, co, h, batch, ex, ew)
+    ref, mag = product64(x, w)
+    assert (np.abs(run_1x1(x, w) - ref) <= SUM_TOL * mag).all()
+
+
+def test_split_tiny_pixel():
+    """A tiny pixel among ordinary ones, an exactly zero one and a filter of
+    zeros: the tiny one keeps its bits."""
+    x, w = split_operands(256, 64, 12, 2)
+    w[5] = 0
+    x[1, :, 3, 4] = np.ldexp(x[1, :, 3, 4], -130)
+    x[0, :, 7, 7] = 0
+    w *= np.float32(2.0 ** 100)
+    ref, mag = product64(x, w)
+    got = run_1x1(x, w)
+    assert (np.abs(got - ref) <= SUM_TOL * mag).all()
+    assert (got[:, 5] == 0).all() and (got[0, :, 7, 7] == 0).all() and (got[1, :5, 3, 4] != 0).all()
