@@ -5,11 +5,15 @@
 // TFLOP/s), and the fp32 layers of a partition were bound by it.  A float has
 // 24 significant bits and a bf16 eight, so x = x0 + x1 + x2 with
 //     x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1
-// (rounded to nearest even; both differences are exact, and x2 fits a bf16).
+// (rounded to nearest even; both differences are exact, and x2 fits a bf16), the
+// splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype for Higher-Precision Computations" (ARITH 2019).
 // A product of two such sums has nine terms; the three smallest (x1 w2, x2 w1,
-// x2 w2, together below 2^-25 of |x w|) are left out and the other six are
-// accumulated in fp32 by v_mfma_f32_16x16x32_bf16, whose 16-bit products are
-// exact.  Nothing is stored or summed in 16 bits: the planes together hold the
+// x2 w2) are left out and the other six are accumulated in fp32 by
+// v_mfma_f32_16x16x32_bf16, whose 16-bit products are exact.  |x1| is at most
+// 2^-8 and |x2| 2^-17 of |x|, so the terms left out stay below 2^-24 of |x w|,
+// one rounding to fp32 (2^-28 on average); a product that fits fp32 has none of
+// them.  Nothing is stored or summed in 16 bits: the planes together hold the
 // fp32 value.  The fp32 accumulator is rounded six times per 32 k instead of
 // at each of eight K = 4 instructions, and the error against 64-bit sums is no
 // larger than the fp32 instruction's (figures at the dispatch rule).  Work per
