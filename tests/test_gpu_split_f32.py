@@ -150,3 +150,84 @@ def test_split_tiny_pixel():
     got = run_1x1(x, w)
     assert (np.abs(got - ref) <= SUM_TOL * mag).all()
     assert (got[:, 5] == 0).all() and (got[0, :, 7, 7] == 0).all() and (got[1, :5, 3, 4] != 0).all()
+
+
+# (tile, C, Co, H, batch) of 1x1 layers, K tail of 4 in three of them
+TILES_1X1 = [("32x32", 260, 68, 12, 2), ("32x64", 260, 512, 29, 1), ("64x64", 256, 260, 30, 4),
+             ("64x128", 260, 260, 64, 2)]
+
+
+def tile_of(c, co, h, batch):
+    from paper_2507_18748_amd import Partition
+    m = make((c, h, h), [conv("c", -1, c, co, act="none", bn=False)])
+    with Partition(m.layers, {0: {"weight": np.zeros((co, c, 1, 1), np.float32)}}, (c, h, h), 0, 1,
+                   "f32", max_batch=batch) as part:
+        return part.layer_info(0, batch)["kernel"]
+
+
+@pytest.mark.parametrize("tile,c,co,h,batch", TILES_1X1)
+def test_split_accuracy(tile, c, co, h, batch):
+    """Every plane of both operands counts.  Random terms: an error of 2^-24 of
+    each product and of a few partial sums averages below 1.5e-7 of the result
+    (2-norm); a plane less gives 2e-6.  Mantissas whose lower planes all have
+    one sign: below three roundings of 2^-24, a plane less gives 2^-17."""
+    assert tile_of(c, co, h, batch).startswith(f"conv_gemm_split<f32,{tile}> ")
+    x, w = split_operands(c, co, h, batch)
+    ref, _ = product64(x, w)
+    assert np.linalg.norm(run_1x1(x, w) - ref) <= 1.5e-7 * np.linalg.norm(ref)
+    v = np.float32(1 + 2.0 ** -8 + 2.0 ** -15 + 2.0 ** -23)
+    for a, b in ((v, v), (v, 1), (1, v)):
+        ref, _ = product64(np.full_like(x, a), np.full_like(w, b))
+        got = run_1x1(np.full_like(x, a), np.full_like(w, b))
+        assert np.abs(got / ref - 1).max() <= 3 * 2.0 ** -24
+
+
+def same_as_f32(m, P, x):
+    """The split kernel against the fp32 matrix instruction, non-finite values
+    and element by element: both are fp32 sums of the same terms, each within
+    SUM_TOL of the sum of their magnitudes."""
+    from paper_2507_18748_amd import Partition
+    outs = []
+    for tuning in (None, {"gemm_plan": (9, 0, 1)}):
+        with Partition(m.layers, P, x.shape[1:], 0, 1, "f32", max_batch=x.shape[0],
+                       tuning=tuning) as part:
+            name = part.layer_info(0, x.shape[0])["kernel"]
+            assert name.startswith("conv_gemm<f32" if tuning else "conv_gemm_split<")
+            outs.append(gpu_forward(part, x))
+    got, want = outs
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+    np.testing.assert_array_equal(np.isinf(got), np.isinf(want))
+    np.testing.assert_array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    fin = np.isfinite(want)
+    with np.errstate(invalid="ignore"):
+        mag = product64(x, P[0]["weight"])[1][fin]
+    err = np.abs(got[fin].astype(np.float64) - want[fin])
+    assert (err <= 2 * SUM_TOL * mag).all(), (err / mag).max()
+    return want
+
+
+@pytest.mark.parametrize("tile,c,co,h,batch", TILES_1X1)
+def test_split_non_finite_weights(tile, c, co, h, batch):
+    """Infinite, NaN and huge weights (3.4e38 rounds to an infinite bf16, 1e33
+    overflows when scaled) in the first, middle and last chunk."""
+    x, w = split_operands(c, co, h, batch, ew=-4)
+    x[:, :, 1, 2] = 0                     # 0 * inf there
+    x *= np.float32(2.0 ** -6)
+    w[3, 7], w[20, c // 2], w[41, c - 1], w[66, 9] = np.inf, np.nan, 3.4e38, 1e33
+    m = make((c, h, h), [conv("c", -1, c, co, act="none", bn=False)])
+    want = same_as_f32(m, {0: {"weight": w}}, x)
+    # (the epilogue's clamp turns NaN into -inf)
+    assert (want[:, 3, 1, 2] == -np.inf).all() and (want[:, 3] == np.inf).any()
+    assert (want[:, 20] == -np.inf).all() and np.isfinite(want[:, 66]).all()
+
+
+@pytest.mark.parametrize("tile,c,co,h,batch", [t for t in TILES_1X1 if t[1] % 32])
+def test_split_non_finite_after_tail(tile, c, co, h, batch):
+    """The last chunk of 260 channels reads on into the next pixel's first ones,
+    under zero weights: what is there does not reach the pixel."""
+    x, w = split_operands(c, co, h, batch)
+    x[0, 5, 0, 1], x[0, 20, 3, 0], x[-1, 0, h - 1, h - 1] = np.inf, np.nan, 3.4e38
+    m = make((c, h, h), [conv("c", -1, c, co, act="none", bn=False)])
+    want = same_as_f32(m, {0: {"weight": w}}, x)
+    assert np.isfinite(want[0, :, 0, 0]).all() and np.isfinite(want[0, :, 2, h - 1]).all()
+    assert not np.isfinite(want[0, :, 0, 1]).any()
