@@ -186,6 +186,7 @@ ppipe_partition* ppipe_partition_create_on_share(const ppipe_model_desc* desc,
  * in:  device pointer, [batch][in_h][in_w][in_c] in dtype (caller-owned).
  * out: device pointer, [batch][out_h][out_w][out_c] in out_dtype (caller-owned);
  *      [batch][classes] fp32 probabilities when the range ends with FC_SOFTMAX.
+ *      in == out is refused (PPIPE_E_INVALID).
  * stream: a hipStream_t (NULL = default stream).  Asynchronous: enqueues work
  * on the stream and returns; no host synchronisation, no allocation.  If a
  * graph for (batch, in, out) was captured with ppipe_partition_capture it is

@@ -700,6 +700,27 @@ hipError_t enqueue_layer(const ppipe_partition* P, const LayerRT& l, int batch, 
     }
 }
 
+// Whether the caller's input and output buffers share bytes.
+bool buffers_overlap(const ppipe_partition* P, int batch, const void* in, const void* out)
+{
+    const uintptr_t i = (uintptr_t)in, o = (uintptr_t)out;
+    const size_t in_b = (size_t)batch * P->in.c * P->in.h * P->in.w * dtype_size(P->dtype);
+    const size_t out_b = (size_t)batch * P->out.c * P->out.h * P->out.w * dtype_size(P->out_dtype);
+    return i < o + out_b && o < i + in_b;
+}
+
+// Whether the block that starts at position i runs as one launch.  Its blocks
+// read the input's halos while others write the output, so a partition that is
+// this block alone takes the three launches when the caller's buffers share
+// bytes (the first of them has read all of the input before the last one writes).
+bool fuse_runs(const ppipe_partition* P, size_t i, int batch, const void* in, const void* out)
+{
+    const LayerRT& l = P->L[i];
+    return l.fuse && l.fuse_plans[batch - 1].on &&
+           !(l.in_buf == BUF_IN && P->L[i + 2].out_buf == BUF_OUT &&
+             buffers_overlap(P, batch, in, out));
+}
+
 // The block that starts at position i as one launch.
 hipError_t enqueue_fused(const ppipe_partition* P, size_t i, int batch, const void* in, void* out,
                          hipStream_t s)
@@ -735,7 +756,7 @@ hipError_t enqueue_all(const ppipe_partition* P, int batch, const void* in, void
     for (size_t i = 0; i < P->L.size(); ++i) {
         const LayerRT& l = P->L[i];
         hipError_t e;
-        if (!hook && l.fuse && l.fuse_plans[batch - 1].on) {
+        if (!hook && fuse_runs(P, i, batch, in, out)) {
             e = enqueue_fused(P, i, batch, in, out, s);
             i += 2;
         } else if (!hook && l.pair >= 0 && pair_runs(P, l.pair_lead ? l : P->L[l.pair],

@@ -74,3 +74,34 @@ def test_not_fused():
         with Partition(m.layers, W.model_params(m, 0, "f16"), (c, h, h), 0, 5, "f16",
                        max_batch=2) as part:
             assert not any("fused" in part.layer_info(i, 2)["kernel"] for i in range(5))
+
+
+@pytest.mark.parametrize("offset", ["before", "after", "inside"])
+@pytest.mark.parametrize("capture", [False, True])
+def test_overlapping_buffers(offset, capture):
+    """A partition that is one block, its output written over part of its input:
+    the input is read whole first.  The same pointer twice stays refused."""
+    import torch
+    from paper_2507_18748_amd import Partition, PpipeError
+    n, c, h, w = 2, 24, 40, 36
+    m = make((c, h, w), block(c, 72, c, 1, 1, False, ("relu6", "relu6", "none"))[1:4])
+    for i, L in enumerate(m.layers):
+        L.src = i - 1
+    P = W.model_params(m, 0, "f16")
+    x = W.partition_input((c, h, w), n, 0, "f16", "normal")
+    nb = n * c * h * w
+    with Partition(m.layers, P, (c, h, w), 0, 3, "f16", max_batch=n) as part:
+        assert "fused=0-2" in part.layer_info(0, n)["kernel"]
+        want = gpu_forward(part, x)
+        buf = torch.zeros(3 * nb, dtype=torch.float16, device="cuda")
+        xin, k = buf[nb:2 * nb], {"before": nb - 48 * w, "after": nb + 48 * w, "inside": nb + 8}[offset]
+        out = buf[k:k + nb]
+        xin.copy_(torch.from_numpy(x.transpose(0, 2, 3, 1).reshape(-1)).half())
+        if capture:
+            part.capture(n, xin.data_ptr(), out.data_ptr())
+        part.run(n, xin.data_ptr(), out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got = out.reshape(n, h, w, c).float().cpu().numpy().transpose(0, 3, 1, 2)
+        np.testing.assert_array_equal(got, want)
+        with pytest.raises(PpipeError):
+            part.run(n, xin.data_ptr(), xin.data_ptr(), 0)
