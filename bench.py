@@ -215,6 +215,19 @@ def batch_sweep(part, max_batch, xd, out, stream, batches, steps=20, rounds=3):
     return res
 
 
+def layer_work(part, i, batch):
+    """FLOPs and bytes of layer i's launch at a batch; of the whole launch where
+    the layer is one of an inverted-residual block's ("fused=I-K"), whose inner
+    maps do not leave the chip."""
+    import re
+    li = part.layer_info(i, batch)
+    m = re.search(r"fused=(\d+)-(\d+)", li["kernel"])
+    ls = [part.layer_info(k, batch) for k in range(int(m[1]), int(m[2]) + 1)] if m else [li]
+    act = sum(k["act_bytes_b1"] for k in ls) - 2 * sum(k["out_bytes_b1"] for k in ls[:-1])
+    return (batch * sum(k["flops_b1"] for k in ls),
+            batch * act + sum(k["param_bytes"] for k in ls), [k["index"] for k in ls])
+
+
 def write_table_json(path, out):
     """Writes a latency table compactly: per-batch lists aligned with
     out["batches"] (microseconds to 0.01, fractions to 4 digits), a layer's
@@ -547,12 +560,10 @@ def latency_table(args):
                "S_i_bytes": info["out_bytes_b1"], "out_chw": [info["out_c"], info["out_h"], info["out_w"]],
                "us": [], "roofline_frac": [], "bound": []}
         for j, b in enumerate(batches):
-            li = part.layer_info(i, b)
-            fl = b * li["flops_b1"]
-            by = b * li["act_bytes_b1"] + li["param_bytes"]
+            fl, by, ls = layer_work(part, i, b)
             t_roof = max(fl / peak_f, by / peak_b)
-            us = float(table[i - wl.begin, j])
-            row["us"].append(us)
+            us = float(sum(table[k - wl.begin, j] for k in ls))
+            row["us"].append(float(table[i - wl.begin, j]))
             row["roofline_frac"].append(t_roof * 1e6 / us if us > 0 else None)
             row["bound"].append("mfma" if fl / peak_f >= by / peak_b else "hbm")
         row["kernel_at_max_batch"] = info["kernel"]

@@ -111,7 +111,8 @@ typedef struct {
     int32_t index;                   /* global layer index */
     int32_t op;                      /* ppipe_op */
     int32_t out_c, out_h, out_w;
-    int32_t kernel_count;            /* launches this layer issues at the queried batch */
+    int32_t kernel_count;            /* launches this layer issues at the queried batch; of the
+                                        layers of one launch ("fused=I-K") I has 1, the others 0 */
     int64_t out_bytes_b1;            /* S_i: output feature-map bytes at batch 1 */
     double flops_b1;                 /* algorithmic FLOPs at batch 1 (2 per multiply-add) */
     double act_bytes_b1;             /* input + output (+ residual) activation bytes at batch 1 */
@@ -195,9 +196,9 @@ ppipe_partition* ppipe_partition_create_on_share(const ppipe_model_desc* desc,
  * convolution and its downsample projection) go out as one launch when both
  * are planned on the same tile configuration without a K split, and so do the
  * three layers of an inverted-residual block (1x1 expansion, depthwise, 1x1
- * projection) of few channels; timed and profiled runs keep one launch
- * sequence per layer.  Concurrent runs of
- * one handle on different streams race on its buffers. */
+ * projection) of few channels.  Timed and profiled runs issue a block's one
+ * launch too, and record it at its first layer, but keep paired layers apart.
+ * Concurrent runs of one handle on different streams race on its buffers. */
 int ppipe_partition_run(ppipe_partition* h, int32_t batch, const void* in,
                         void* out, void* stream);
 
@@ -233,7 +234,9 @@ int ppipe_partition_capture(ppipe_partition* h, int32_t batch, const void* in,
  * stream, each layer's first kernel launch recording a HIP event before it
  * and its last launch one after it (events recorded by the launches
  * themselves, nothing between the kernels); out_us[i * n_batches + j] =
- * median microseconds of layer begin + i over the runs.  out_partition_us[j]
+ * median microseconds of layer begin + i over the runs (the layers of a block
+ * that runs as one launch share its time by their FLOPs; a layer whose launch
+ * reads the next layer's weights ahead has that in its time).  out_partition_us[j]
  * = median over three trials of the whole range replayed `reps` times back
  * to back as one captured HIP graph (per replay).  Either output may be NULL.
  * Allocates its own input and output buffers, synchronises internally.

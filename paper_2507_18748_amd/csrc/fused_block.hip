@@ -352,4 +352,11 @@ hipError_t launch_fused_block(int dt, const FusedBlockArgs& a, hipStream_t s)
     }
 }
 
+const char* fused_block_name(int dt, int stride)
+{
+    static const char* n[2][2] = {{"fused_block<f16,s1>", "fused_block<f16,s2>"},
+                                  {"fused_block<bf16,s1>", "fused_block<bf16,s2>"}};
+    return n[dt == DT_BF16][stride == 2];
+}
+
 }  // namespace ppipe

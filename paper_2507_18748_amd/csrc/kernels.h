@@ -286,6 +286,7 @@ constexpr int FUSED_MAX_C = 32, FUSED_MAX_CE = 192, FUSED_MAX_CO = 64;
 // Output tile of at most 64 pixels: the fewest tiles, then the smallest halo.
 void fused_block_tile(int Ho, int Wo, int stride, int* TH, int* TW);
 hipError_t launch_fused_block(int dt, const FusedBlockArgs& a, hipStream_t s);
+const char* fused_block_name(int dt, int stride);
 
 // k x k max pooling, NHWC; out-of-range taps never win.
 hipError_t launch_maxpool(int dt, const void* x, void* y, int N, int H, int W, int C,

@@ -145,8 +145,9 @@ struct LayerRT {
     int pair = -1;
     bool pair_lead = false;
     // first of the three layers of an inverted-residual block, and the plan of
-    // the one launch per batch
+    // the one launch per batch; fuse_pos: 0, 1, 2 on the three, -1 elsewhere
     bool fuse = false;
+    int fuse_pos = -1;
     std::vector<FusePlan> fuse_plans;
     std::vector<Plan> plans;   // [batch - 1]
     std::string name;          // the description's layer name, or "layer<i>"
@@ -488,7 +489,35 @@ std::vector<int> launch_roles(const LayerRT& l, int batch)
     return r;
 }
 
-int layer_launches(const LayerRT& l, int batch) { return (int)launch_roles(l, batch).size(); }
+// Whether the range's last block must run layer by layer: its launch reads the
+// input's halos in some blocks while others write the output, so where it does
+// both on the caller's buffers and those share bytes, it takes the three
+// launches (the first has read all of the input before the last writes).
+bool last_block_apart(const ppipe_partition* P, int batch, const void* in, const void* out)
+{
+    const size_t n = P->L.size();
+    if (n < 3 || !P->L[n - 3].fuse || P->L[n - 3].in_buf != BUF_IN) return false;
+    const uintptr_t i = (uintptr_t)in, o = (uintptr_t)out;
+    const size_t in_b = (size_t)batch * P->in.c * P->in.h * P->in.w * dtype_size(P->dtype);
+    const size_t out_b = (size_t)batch * P->out.c * P->out.h * P->out.w * dtype_size(P->out_dtype);
+    return i < o + out_b && o < i + in_b;
+}
+
+// Whether the layer runs in the one launch of an inverted-residual block
+// (apart: last_block_apart of the caller's buffers).
+bool fuse_runs(const ppipe_partition* P, const LayerRT& l, int batch, bool apart)
+{
+    const size_t i = &l - P->L.data();
+    return l.fuse_pos >= 0 && P->L[i - l.fuse_pos].fuse_plans[batch - 1].on &&
+           !(apart && i + 3 >= P->L.size());
+}
+
+// Launches of one layer; a block's one launch counts as its first layer's.
+int layer_launches(const ppipe_partition* P, const LayerRT& l, int batch, bool apart = false)
+{
+    if (fuse_runs(P, l, batch, apart)) return l.fuse_pos == 0 ? 1 : 0;
+    return (int)launch_roles(l, batch).size();
+}
 
 std::string launch_name(const ppipe_partition* P, const LayerRT& l, int batch, int launch)
 {
@@ -508,14 +537,31 @@ std::string launch_name(const ppipe_partition* P, const LayerRT& l, int batch, i
     }
 }
 
+// The same for a run's records, where a block's one launch goes by its own name.
+std::string record_name(const ppipe_partition* P, const LayerRT& l, int batch, int launch,
+                        bool apart = false)
+{
+    return fuse_runs(P, l, batch, apart) ? fused_block_name(P->dtype, (&l)[1].stride)
+                                               : launch_name(P, l, batch, launch);
+}
+
 // Algorithmic work of one launch: FLOPs, and the layer's input, weight,
 // output and residual bytes each counted once.  In a multi-launch layer the
 // first launch owns the input (the GEMM also the weights and FLOPs) and the
 // last launch the output and residual; a split-K reduction in between owns
-// nothing.
+// nothing.  A block's one launch owns the FLOPs and weights of its three
+// layers, the first one's input and the last one's output and residual.
 void launch_work(const ppipe_partition* P, const LayerRT& l, int batch, int launch,
-                 double* flops, double* bytes)
+                 double* flops, double* bytes, bool apart = false)
 {
+    if (fuse_runs(P, l, batch, apart)) {
+        const LayerRT* q = &l;
+        const LayerRT& last = q[2];
+        *flops = batch * (q[0].flops_b1 + q[1].flops_b1 + last.flops_b1);
+        *bytes = batch * (l.in_bytes_b1 + last.res_bytes_b1 + (double)last.out_bytes_b1) +
+                 q[0].param_bytes + q[1].param_bytes + last.param_bytes;
+        return;
+    }
     const double b = batch;
     const double out_bytes = b * (double)l.out_bytes_b1 *
                              (l.softmax ? 4.0 / dtype_size(P->dtype) : 1.0);
@@ -700,27 +746,6 @@ hipError_t enqueue_layer(const ppipe_partition* P, const LayerRT& l, int batch, 
     }
 }
 
-// Whether the caller's input and output buffers share bytes.
-bool buffers_overlap(const ppipe_partition* P, int batch, const void* in, const void* out)
-{
-    const uintptr_t i = (uintptr_t)in, o = (uintptr_t)out;
-    const size_t in_b = (size_t)batch * P->in.c * P->in.h * P->in.w * dtype_size(P->dtype);
-    const size_t out_b = (size_t)batch * P->out.c * P->out.h * P->out.w * dtype_size(P->out_dtype);
-    return i < o + out_b && o < i + in_b;
-}
-
-// Whether the block that starts at position i runs as one launch.  Its blocks
-// read the input's halos while others write the output, so a partition that is
-// this block alone takes the three launches when the caller's buffers share
-// bytes (the first of them has read all of the input before the last one writes).
-bool fuse_runs(const ppipe_partition* P, size_t i, int batch, const void* in, const void* out)
-{
-    const LayerRT& l = P->L[i];
-    return l.fuse && l.fuse_plans[batch - 1].on &&
-           !(l.in_buf == BUF_IN && P->L[i + 2].out_buf == BUF_OUT &&
-             buffers_overlap(P, batch, in, out));
-}
-
 // The block that starts at position i as one launch.
 hipError_t enqueue_fused(const ppipe_partition* P, size_t i, int batch, const void* in, void* out,
                          hipStream_t s)
@@ -745,19 +770,32 @@ hipError_t enqueue_fused(const ppipe_partition* P, size_t i, int batch, const vo
     return launch_fused_block(P->dtype, a, s);
 }
 
-// The whole range in layer order.  Without a hook (the run and capture
-// paths), paired layers whose plans allow it go out as one launch at the
-// lead's position, and so does an inverted-residual block; runs with a hook (per-layer and per-launch timing) keep
-// one launch sequence per layer.
+// One launch of a layer (its j-th; a block's one launch at its first layer),
+// for the profilers' own buffers.
+hipError_t enqueue_launch(const ppipe_partition* P, const LayerRT& l, int batch, const void* in,
+                          void* out, hipStream_t s, int j)
+{
+    return fuse_runs(P, l, batch, false)
+               ? enqueue_fused(P, &l - P->L.data(), batch, in, out, s)
+               : enqueue_layer(P, l, batch, in, out, s, nullptr, j);
+}
+
+// The whole range in layer order, inverted-residual blocks as one launch where
+// planned.  Without a hook (the run and capture paths), paired layers whose
+// plans allow it go out as one launch at the lead's position; runs with a hook
+// (per-layer and per-launch timing) keep them apart.
 hipError_t enqueue_all(const ppipe_partition* P, int batch, const void* in, void* out,
                        hipStream_t s, LaunchHook* hook, const Workspace* wsp = nullptr)
 {
     const Workspace W = wsp ? *wsp : handle_workspace(P);
+    const bool apart = last_block_apart(P, batch, in, out);
     for (size_t i = 0; i < P->L.size(); ++i) {
         const LayerRT& l = P->L[i];
         hipError_t e;
-        if (!hook && fuse_runs(P, i, batch, in, out)) {
+        if (fuse_runs(P, l, batch, apart)) {
+            if (hook) hook->before(l, 0, s);
             e = enqueue_fused(P, i, batch, in, out, s);
+            if (hook) hook->after(l, 0, s);
             i += 2;
         } else if (!hook && l.pair >= 0 && pair_runs(P, l.pair_lead ? l : P->L[l.pair],
                                               l.pair_lead ? P->L[l.pair] : l, batch)) {
@@ -1144,6 +1182,7 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
             dw.kind == K_DW && dw.C <= FUSED_MAX_CE && feeds_next(i + 1) && plain_1x1(pr) &&
             pr.Co <= FUSED_MAX_CO && pr.pair < 0 && pr.res_src < i) {
             l.fuse = true;
+            for (int q = 0; q < 3; ++q) P->L[i - begin + q].fuse_pos = q;
             i += 2;
         }
     }
@@ -1363,21 +1402,20 @@ struct EventPool {
 // Hands layer i's event pair to its first launch (start) and its last launch
 // (stop), so that the pair spans the layer's kernels in a run.
 struct LayerEventsHook : LaunchHook {
-    LayerEventsHook(const std::vector<hipEvent_t>& e, int b) : ev(e), batch(b) {}
+    LayerEventsHook(const ppipe_partition* p, const std::vector<hipEvent_t>& e, int b)
+        : P(p), ev(e), batch(b) {}
     ~LayerEventsHook() override { launch_events() = LaunchEvents{}; }
+    const ppipe_partition* P;
     const std::vector<hipEvent_t>& ev;
-    int batch, layer = 0;
+    int batch;
     void before(const LayerRT& l, int li, hipStream_t) override
     {
-        const int n = layer_launches(l, batch);
-        launch_events() = LaunchEvents{li == 0 ? ev[2 * layer] : nullptr,
-                                       li == n - 1 ? ev[2 * layer + 1] : nullptr};
+        const size_t i = &l - P->L.data();
+        launch_events() =
+            LaunchEvents{li == 0 ? ev[2 * i] : nullptr,
+                         li == layer_launches(P, l, batch) - 1 ? ev[2 * i + 1] : nullptr};
     }
-    void after(const LayerRT& l, int li, hipStream_t) override
-    {
-        launch_events() = LaunchEvents{};
-        if (li == layer_launches(l, batch) - 1) ++layer;
-    }
+    void after(const LayerRT&, int, hipStream_t) override { launch_events() = LaunchEvents{}; }
 };
 
 template <typename F>
@@ -1677,13 +1715,22 @@ int ppipe_profile_layers(ppipe_partition* h, const int32_t* batch_sizes, int32_t
         // i's time runs from its first kernel's start to its last kernel's end
         std::vector<std::vector<float>> t(nl);
         for (int r = 0; r < reps && e == hipSuccess; ++r) {
-            LayerEventsHook hook(lev.ev, b);
+            LayerEventsHook hook(h, lev.ev, b);
             e = enqueue_all(h, b, pb.in, pb.out, pb.s, &hook);
             if (e == hipSuccess) e = hipStreamSynchronize(pb.s);
             for (int i = 0; i < nl && e == hipSuccess; ++i) {
                 float ms = 0;
                 e = hipEventElapsedTime(&ms, lev.ev[2 * i], lev.ev[2 * i + 1]);
-                t[i].push_back(ms * 1000.0f);
+                if (!fuse_runs(h, h->L[i], b, false)) {
+                    t[i].push_back(ms * 1000.0f);
+                    continue;
+                }
+                // a block's launch: each layer its share by FLOPs
+                const LayerRT* l = &h->L[i];
+                const double sum = l[0].flops_b1 + l[1].flops_b1 + l[2].flops_b1;
+                for (int q = 0; q < 3; ++q)
+                    t[i + q].push_back((float)(ms * 1000.0 * l[q].flops_b1 / sum));
+                i += 2;
             }
         }
         if (e != hipSuccess) return fail(PPIPE_E_HIP, hip_msg("profile run", e));
@@ -1719,7 +1766,7 @@ int ppipe_profile_kernels(ppipe_partition* h, int32_t batch, int32_t warmup, int
     int rc = ensure_device(h);
     if (rc != PPIPE_OK) return rc;
     int nlaunch = 0;
-    for (const LayerRT& l : h->L) nlaunch += layer_launches(l, batch);
+    for (const LayerRT& l : h->L) nlaunch += layer_launches(h, l, batch);
     *count = nlaunch;
     ProfileBuffers pb;
     if ((rc = setup_profile(h, pb)) != PPIPE_OK) return rc;
@@ -1731,11 +1778,11 @@ int ppipe_profile_kernels(ppipe_partition* h, int32_t batch, int32_t warmup, int
     if (e != hipSuccess) return fail(PPIPE_E_HIP, hip_msg("kernel launch", e));
     int k = 0;
     for (const LayerRT& l : h->L) {
-        for (int j = 0; j < layer_launches(l, batch); ++j, ++k) {
+        for (int j = 0; j < layer_launches(h, l, batch); ++j, ++k) {
             std::vector<float> t;
             for (int q = 0; q < PROFILE_TRIALS && e == hipSuccess; ++q)
                 e = time_reps(pb.s, ev, reps, [&] {
-                    return enqueue_layer(h, l, batch, pb.in, pb.out, pb.s, nullptr, j);
+                    return enqueue_launch(h, l, batch, pb.in, pb.out, pb.s, j);
                 }, t);
             if (e != hipSuccess) return fail(PPIPE_E_HIP, hip_msg("profile run", e));
             if (!records || k >= capacity) continue;
@@ -1744,7 +1791,7 @@ int ppipe_profile_kernels(ppipe_partition* h, int32_t batch, int32_t warmup, int
             rec.layer = l.index;
             rec.launch = j;
             std::snprintf(rec.kernel, sizeof(rec.kernel), "%s",
-                          launch_name(h, l, batch, j).c_str());
+                          record_name(h, l, batch, j).c_str());
             launch_work(h, l, batch, j, &rec.flops, &rec.bytes);
             double sum = 0;
             for (float v : t) sum += v;
@@ -1766,7 +1813,7 @@ int ppipe_profile_kernels_cold(ppipe_partition* h, int32_t batch, int32_t reps,
     int rc = ensure_device(h);
     if (rc != PPIPE_OK) return rc;
     int nlaunch = 0;
-    for (const LayerRT& l : h->L) nlaunch += layer_launches(l, batch);
+    for (const LayerRT& l : h->L) nlaunch += layer_launches(h, l, batch);
     *count = nlaunch;
     ProfileBuffers pb;
     if ((rc = setup_profile(h, pb)) != PPIPE_OK) return rc;
@@ -1785,13 +1832,13 @@ int ppipe_profile_kernels_cold(ppipe_partition* h, int32_t batch, int32_t reps,
         return fail(PPIPE_E_HIP, hip_msg("kernel launch", e));
     int k = 0;
     for (const LayerRT& l : h->L) {
-        for (int j = 0; j < layer_launches(l, batch); ++j, ++k) {
+        for (int j = 0; j < layer_launches(h, l, batch); ++j, ++k) {
             std::vector<float> t;
             for (int r = 0; r < reps && e == hipSuccess; ++r) {
                 e = launch_cache_sweep(sw.p, (size_t)sweep_bytes, pb.s);
                 if (e != hipSuccess) break;
                 launch_events() = LaunchEvents{ev.a, ev.b};
-                e = enqueue_layer(h, l, batch, pb.in, pb.out, pb.s, nullptr, j);
+                e = enqueue_launch(h, l, batch, pb.in, pb.out, pb.s, j);
                 launch_events() = LaunchEvents{};
                 if (e == hipSuccess) e = hipEventSynchronize(ev.b);
                 float ms = 0;
@@ -1805,7 +1852,7 @@ int ppipe_profile_kernels_cold(ppipe_partition* h, int32_t batch, int32_t reps,
             rec.layer = l.index;
             rec.launch = j;
             std::snprintf(rec.kernel, sizeof(rec.kernel), "%s",
-                          launch_name(h, l, batch, j).c_str());
+                          record_name(h, l, batch, j).c_str());
             launch_work(h, l, batch, j, &rec.flops, &rec.bytes);
             double sum = 0;
             for (float v : t) sum += v;
@@ -1932,8 +1979,9 @@ int ppipe_timing_setup(ppipe_partition* h, int32_t batch, const void* in, void* 
     // event is recorded after its last launch on the same stream
     if (h->timed.ran && !h->timed.ev.empty()) (void)hipEventSynchronize(h->timed.ev.back());
     release_timed(h);
+    const bool apart = last_block_apart(h, batch, in, out);
     int nlaunch = 0;
-    for (const LayerRT& l : h->L) nlaunch += layer_launches(l, batch);
+    for (const LayerRT& l : h->L) nlaunch += layer_launches(h, l, batch, apart);
     h->timed.ev.assign(2 * (size_t)nlaunch, nullptr);
     for (hipEvent_t& e : h->timed.ev) {
         const hipError_t he = hipEventCreate(&e);
@@ -1972,9 +2020,10 @@ int ppipe_timing_read(ppipe_partition* h, ppipe_kernel_record* records, int32_t 
     hipError_t e = hipEventSynchronize(h->timed.ev.back());
     if (e != hipSuccess) return fail(PPIPE_E_HIP, hip_msg("hipEventSynchronize", e));
     const int batch = h->timed.batch;
+    const bool apart = last_block_apart(h, batch, h->timed.in, h->timed.out);
     int k = 0;
     for (const LayerRT& l : h->L) {
-        for (int j = 0; j < layer_launches(l, batch); ++j, ++k) {
+        for (int j = 0; j < layer_launches(h, l, batch, apart); ++j, ++k) {
             if (!records || k >= capacity) continue;
             float ms = 0;
             e = hipEventElapsedTime(&ms, h->timed.ev[2 * k], h->timed.ev[2 * k + 1]);
@@ -1984,8 +2033,8 @@ int ppipe_timing_read(ppipe_partition* h, ppipe_kernel_record* records, int32_t 
             rec.layer = l.index;
             rec.launch = j;
             std::snprintf(rec.kernel, sizeof(rec.kernel), "%s",
-                          launch_name(h, l, batch, j).c_str());
-            launch_work(h, l, batch, j, &rec.flops, &rec.bytes);
+                          record_name(h, l, batch, j, apart).c_str());
+            launch_work(h, l, batch, j, &rec.flops, &rec.bytes, apart);
             rec.mean_us = rec.median_us = rec.min_us = ms * 1000.0f;
         }
     }
@@ -2029,7 +2078,7 @@ int ppipe_layer_info(const ppipe_partition* h, int32_t index, int32_t batch,
     info->op = l.op;
     std::snprintf(info->name, sizeof(info->name), "%s", l.name.c_str());
     info->out_c = l.Co; info->out_h = l.Ho; info->out_w = l.Wo;
-    info->kernel_count = layer_launches(l, batch);
+    info->kernel_count = layer_launches(h, l, batch);
     info->out_bytes_b1 = l.softmax ? (int64_t)l.Co * 4 : l.out_bytes_b1;
     info->flops_b1 = l.flops_b1;
     info->act_bytes_b1 = l.in_bytes_b1 + l.res_bytes_b1 + (double)info->out_bytes_b1;
@@ -2050,9 +2099,9 @@ int ppipe_layer_info(const ppipe_partition* h, int32_t index, int32_t batch,
         info->forced = p.forced ? 1 : 0;
     }
     if (l.kind == K_DW && h->tune.dw_outputs) info->forced = 1;
-    for (int i = std::max(0, l.index - h->begin - 2); i <= l.index - h->begin; ++i)
-        if (h->L[i].fuse && h->L[i].fuse_plans[batch - 1].on)
-            k += " fused=" + std::to_string(h->L[i].index) + "-" + std::to_string(h->L[i + 2].index);
+    if (fuse_runs(h, l, batch, false))
+        k += " fused=" + std::to_string(l.index - l.fuse_pos) + "-" +
+             std::to_string(l.index - l.fuse_pos + 2);
     std::snprintf(info->kernel, sizeof(info->kernel), "%s", k.c_str());
     return PPIPE_OK;
 }

@@ -105,3 +105,47 @@ def test_overlapping_buffers(offset, capture):
         np.testing.assert_array_equal(got, want)
         with pytest.raises(PpipeError):
             part.run(n, xin.data_ptr(), xin.data_ptr(), 0)
+
+
+def test_timed_runs_issue_the_served_launches():
+    """One record for a block, at its first layer, with the work of the three;
+    the layer table's shares add up to its launch.  With buffers that share
+    bytes a lone block is timed as its three launches."""
+    import torch
+    from paper_2507_18748_amd import Partition
+    n, c, h, w = 4, 24, 56, 56
+    m = make((c, h, w), block(c, 144, c, 1, 1, True, ("relu6", "relu6", "none")))
+    P = W.model_params(m, 0, "bf16")
+    x = W.partition_input((c, h, w), n, 0, "bf16", "normal")
+    with Partition(m.layers, P, (c, h, w), 0, 5, "bf16", max_batch=n) as part:
+        info = [part.layer_info(i, n) for i in range(5)]
+        assert [i["kernel_count"] for i in info] == [1, 1, 0, 0, 1]
+        want = gpu_forward(part, x)
+        xd = torch.from_numpy(x.transpose(0, 2, 3, 1).copy()).bfloat16().cuda()
+        out = torch.zeros((n, h, w, 16), dtype=torch.bfloat16, device="cuda")
+        part.timing_setup(n, xd.data_ptr(), out.data_ptr())
+        part.run_timed(torch.cuda.current_stream().cuda_stream)
+        recs = part.timing_read()
+        np.testing.assert_array_equal(out.float().cpu().numpy().transpose(0, 3, 1, 2), want)
+        for r in (recs, part.profile_kernels(n, 1, 2),
+                  part.profile_kernels_cold(n, reps=1, sweep_bytes=64 << 20)):
+            assert [(k["layer"], k["launch"]) for k in r] == [(0, 0), (1, 0), (4, 0)]
+            assert r[1]["kernel"] == "fused_block<bf16,s1>" and r[1]["mean_us"] > 0
+            assert r[1]["flops"] == n * sum(i["flops_b1"] for i in info[1:4])
+            maps = n * 3 * c * h * w * 2                        # input, residual, output
+            assert r[1]["bytes"] == maps + sum(i["param_bytes"] for i in info[1:4])
+        table, whole = part.profile_layers([1, n], warmup=2, reps=5)
+        assert (table > 0).all()
+        share = [i["flops_b1"] / sum(k["flops_b1"] for k in info[1:4]) for i in info[1:4]]
+        np.testing.assert_allclose(table[1:4, 1] / table[1:4, 1].sum(), share, rtol=1e-5)
+    lone = make((c, h, w), block(c, 72, c, 1, 1, False, ("relu6", "relu6", "none"))[1:4])
+    for i, L in enumerate(lone.layers):
+        L.src = i - 1
+    with Partition(lone.layers, W.model_params(lone, 0, "bf16"), (c, h, w), 0, 3, "bf16",
+                   max_batch=n) as part:
+        buf = torch.zeros(2 * n * c * h * w, dtype=torch.bfloat16, device="cuda")
+        part.timing_setup(n, buf.data_ptr(), buf[8:].data_ptr())
+        part.run_timed(torch.cuda.current_stream().cuda_stream)
+        recs = part.timing_read()
+        assert [r["layer"] for r in recs] == [0, 1, 2] and all(r["mean_us"] > 0 for r in recs)
+        assert not any("fused" in r["kernel"] for r in recs)
