@@ -22,13 +22,22 @@ sys.path.insert(0, ROOT)
 METRIC = "CNN-partition images/sec at batch 1–64; per-layer MFMA % or HBM GB/s"
 PEAK_MFMA_TFLOPS = {"f16": 2516.6, "bf16": 2516.6, "f32": 157.3}
 PEAK_HBM_GBS = 8000.0
+# fp32 GEMMs split into bf16 operands: six bf16 products per fp32 product
+PEAK_SPLIT_F32_TFLOPS = PEAK_MFMA_TFLOPS["bf16"] / 6
 DTYPE_LABEL = {"f32": "f32", "f16": "f16", "bf16": "bf16"}
 DEFAULT_WORKLOAD = "resnet152"
 DEFAULT_BATCH = {"resnet152": 64}
 
 
+def peak_tflops(kernel, dtype):
+    """Matrix-core peak of the instructions a kernel runs on."""
+    return PEAK_SPLIT_F32_TFLOPS if kernel.startswith("conv_gemm_split") else PEAK_MFMA_TFLOPS[dtype]
+
+
 def roofline(records, dtype):
-    """Dominant kernel (largest total time per step) and its position."""
+    """Dominant kernel (largest total time per step) and its position.  Bytes
+    are algorithmic: weights at the storage type's size (the split fp32 kernels
+    read 1.5 times that)."""
     groups = {}
     for r in records:
         g = groups.setdefault(r["kernel"], {"us": 0.0, "flops": 0.0, "bytes": 0.0, "n": 0})
@@ -37,12 +46,13 @@ def roofline(records, dtype):
         g["bytes"] += r["bytes"]
         g["n"] += 1
     name, g = max(groups.items(), key=lambda kv: kv[1]["us"])
-    t_mfma = g["flops"] / (PEAK_MFMA_TFLOPS[dtype] * 1e12)
+    peak = peak_tflops(name, dtype)
+    t_mfma = g["flops"] / (peak * 1e12)
     t_hbm = g["bytes"] / (PEAK_HBM_GBS * 1e9)
     avg_us = g["us"] / g["n"]
     if t_mfma >= t_hbm:
         achieved = g["flops"] / g["n"] / (avg_us * 1e-6) / 1e12
-        out = {"bound": "mfma", "achieved": achieved, "peak": PEAK_MFMA_TFLOPS[dtype],
+        out = {"bound": "mfma", "achieved": achieved, "peak": peak,
                "unit": "TFLOP/s"}
     else:
         achieved = g["bytes"] / g["n"] / (avg_us * 1e-6) / 1e9
@@ -62,16 +72,17 @@ def cold_summary(records, dtype, copy_fit=None):
     """Roofline fractions from isolated-cold launches (caches swept before
     every repetition): per kernel family, HBM fraction bytes-weighted
     (sum of bytes / (peak x sum of time)) for memory-bound families and for
-    GEMM launches the roofline puts on HBM, MFMA fraction FLOP-weighted for
-    GEMM launches it puts on MFMA.  Launches moving < 16 MB are counted
+    GEMM launches the roofline puts on HBM, MFMA fraction (sum of the times at
+    each kernel's peak over the sum of its times) for GEMM launches it puts on
+    MFMA.  Launches moving < 16 MB are counted
     separately as launch-bound.  With a cold-copy fit (copy_reference), each
     memory-bound family also reports, over its launches of at least 16 MB,
     the time a plain device copy of the same bytes takes under the same
     isolated-cold method, summed, over the family's time."""
-    peak_f = PEAK_MFMA_TFLOPS[dtype] * 1e12
     peak_b = PEAK_HBM_GBS * 1e9
     fam = {}
     for r in records:
+        peak_f = peak_tflops(r["kernel"], dtype) * 1e12
         name = r["kernel"].split("<")[0]
         t = r["median_us"] * 1e-6
         if name.startswith("conv_gemm"):
@@ -79,12 +90,12 @@ def cold_summary(records, dtype, copy_fit=None):
                 name = "conv_gemm (MFMA-bound launches)"
             else:
                 name = "conv_gemm (HBM-bound launches)"
-        g = fam.setdefault(name, {"us": 0.0, "bytes": 0.0, "flops": 0.0, "launches": 0,
+        g = fam.setdefault(name, {"us": 0.0, "bytes": 0.0, "mfma_s": 0.0, "launches": 0,
                                   "small_launches": 0, "us_big": 0.0, "bytes_big": 0.0,
                                   "copy_us_big": 0.0})
         g["us"] += r["median_us"]
         g["bytes"] += r["bytes"]
-        g["flops"] += r["flops"]
+        g["mfma_s"] += r["flops"] / peak_f
         g["launches"] += 1
         if r["bytes"] < 16e6:
             g["small_launches"] += 1
@@ -100,7 +111,7 @@ def cold_summary(records, dtype, copy_fit=None):
         d = {"us_per_step": round(g["us"], 2), "launches": g["launches"],
              "launches_under_16MB": g["small_launches"]}
         if "MFMA-bound" in name:
-            d["mfma_frac"] = g["flops"] / (g["us"] * 1e-6 * peak_f)
+            d["mfma_frac"] = g["mfma_s"] / (g["us"] * 1e-6)
         else:
             d["hbm_frac"] = g["bytes"] / (g["us"] * 1e-6 * peak_b)
             if g["us_big"] > 0:
@@ -542,7 +553,6 @@ def latency_table(args):
     torch.cuda.set_device(0)
     part = Partition(m.layers, P, (m.in_c, m.in_h, m.in_w), wl.begin, wl.end, wl.dtype,
                      max_batch=max(batches))
-    peak_f = PEAK_MFMA_TFLOPS[wl.dtype] * 1e12
     peak_b = PEAK_HBM_GBS * 1e9
     rows = []
     table = np.zeros((wl.end - wl.begin, len(batches)))
@@ -561,6 +571,7 @@ def latency_table(args):
                "us": [], "roofline_frac": [], "bound": []}
         for j, b in enumerate(batches):
             fl, by, ls = layer_work(part, i, b)
+            peak_f = peak_tflops(part.layer_info(i, b)["kernel"], wl.dtype) * 1e12
             t_roof = max(fl / peak_f, by / peak_b)
             us = float(sum(table[k - wl.begin, j] for k in ls))
             row["us"].append(float(table[i - wl.begin, j]))
