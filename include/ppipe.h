@@ -117,7 +117,8 @@ typedef struct {
     double flops_b1;                 /* algorithmic FLOPs at batch 1 (2 per multiply-add) */
     double act_bytes_b1;             /* input + output (+ residual) activation bytes at batch 1 */
     double param_bytes;              /* weight bytes in dtype + fp32 scale/bias, once per run */
-    char kernel[96];                 /* kernel configuration chosen at the queried batch;
+    char kernel[96];                 /* kernel configuration chosen at the queried batch, with
+                                        " ahead=J" when its launch also reads layer J's weights;
                                         ends in " paired=J" when the layer runs in one
                                         launch with layer J, in " fused=I-K" when layers
                                         I to K run in one launch */

@@ -1576,6 +1576,13 @@ static hipError_t launch_skinny(int wk, const ConvGemmArgs& a, const PrefetchArg
     return hipGetLastError();
 }
 
+// Whether a 16-bit layer planned on 128x128 four-stage tiles runs the
+// warp-specialised kernel.
+static bool runs_specialised(bool tapv, int splits, bool softmax, int Co)
+{
+    return !tapv && splits == 1 && !softmax && Co % 8 == 0;
+}
+
 template <typename T>
 static hipError_t launch_cfg(int cfg, int wk, bool tapv, const ConvGemmArgs& a,
                              const PrefetchArgs& pf, hipStream_t s)
@@ -1615,7 +1622,7 @@ static hipError_t launch_cfg(int cfg, int wk, bool tapv, const ConvGemmArgs& a,
     case GEMM_DMA_64x64_2W_S3: return launch_dma<T, 64, 64, 1, 2, 3>(tapv, a, pf, s);
     case GEMM_DMA_128x128_8W_S4:
         if constexpr (sizeof(T) == 2)
-            if (!tapv && a.splits == 1 && !a.softmax && a.Co % 8 == 0)
+            if (runs_specialised(tapv, a.splits, a.softmax, a.Co))
                 return launch_ws<T, 128, 128, 2, 4, 4, 8>(a, s);
         return launch_dma<T, 128, 128, 2, 4, 4>(tapv, a, pf, s);
     default:            return hipErrorInvalidValue;
@@ -1655,9 +1662,11 @@ hipError_t launch_conv_gemm_pair(int dt, int cfg, const ConvGemmArgs& a0, const 
     }
 }
 
-bool gemm_prefetches(int cfg)
+bool gemm_prefetches(int dt, int cfg, bool tapv, int splits, bool softmax, int Co)
 {
     const GemmCfgInfo c = gemm_cfg_info(cfg);
+    if (cfg == GEMM_DMA_128x128_8W_S4 && dt != DT_F32 && runs_specialised(tapv, splits, softmax, Co))
+        return false;
     return c.skinny || (c.dma && c.mfma == 16);
 }
 

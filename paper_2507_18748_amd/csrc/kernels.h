@@ -202,11 +202,11 @@ constexpr int SKINNY_MAX_WAVES = 16;
 // wk: waves per block of the skinny kernel (K split), ignored by the LDS kernel.
 // tapv: the LDS kernel looks up each 16-byte K vector's (kh, kw, ci) in a
 // table (channel count a multiple of the vector width but not of the stage).
-// pf: weights to read ahead beside the launch (LDS-direct and skinny kernels;
-// ignored by the others).
+// pf: weights to read ahead beside the launch (LDS-direct and skinny kernels,
+// gemm_prefetches; ignored by the others).
 hipError_t launch_conv_gemm(int dt, int cfg, int wk, bool tapv, const ConvGemmArgs& a,
                             const PrefetchArgs& pf, hipStream_t s);
-bool gemm_prefetches(int cfg);
+bool gemm_prefetches(int dt, int cfg, bool tapv, int splits, bool softmax, int Co);
 // Two layers of one DMA tile configuration, each unsplit and without a
 // softmax, in one launch (blocks of a0 first, then of a1).  The layers must
 // not depend on each other; both take plain per-tap K steps (no per-vector

@@ -638,10 +638,14 @@ bool pair_runs(const ppipe_partition* P, const LayerRT& a, const LayerRT& b, int
 // turn, 360 MB) the whole model takes 1017 -> 979 us; where they are in the
 // memory-side cache already nothing changes (ResNet-50 [44, 56) at batch 8
 // 101.3 -> 101.1 us), and 32 blocks suffice (8: 1004, 16: 984, 64: 979 us).
-PrefetchArgs prefetch_args(const ppipe_partition* P, size_t i, int batch, int cfg, int own)
+// j_out: the position of the layer read ahead for.
+PrefetchArgs prefetch_args(const ppipe_partition* P, size_t i, int batch, int own,
+                           size_t* j_out = nullptr)
 {
     PrefetchArgs f;
-    if (!gemm_prefetches(cfg) || own > P->cus)
+    const LayerRT& l = P->L[i];
+    const Plan& p = l.plans[batch - 1];
+    if (!gemm_prefetches(P->dtype, p.cfg, tapv_of(l, p), p.splits, l.softmax, l.Co) || own > P->cus)
         return f;
     size_t j = i + 1;
     for (; j < P->L.size(); ++j) {
@@ -659,7 +663,19 @@ PrefetchArgs prefetch_args(const ppipe_partition* P, size_t i, int batch, int cf
     f.w = n.w;
     f.bytes = (uint32_t)bytes;
     f.blocks = (int)std::min<int64_t>(32, (bytes + 16383) / 16384);
+    if (j_out) *j_out = j;
     return f;
+}
+
+// Blocks of the launch at position i (a pair's: of both layers).
+int launch_blocks(const ppipe_partition* P, const LayerRT& l, int batch)
+{
+    auto blocks = [&](const LayerRT& k) {
+        const Plan& p = k.plans[batch - 1];
+        return p.tiles_m * p.tiles_co * p.splits;
+    };
+    const bool pair = l.pair_lead && pair_runs(P, l, P->L[l.pair], batch);
+    return blocks(l) + (pair ? blocks(P->L[l.pair]) : 0);
 }
 
 // Enqueue the launches of one layer; only >= 0 restricts to that launch.
@@ -696,7 +712,7 @@ hipError_t enqueue_layer(const ppipe_partition* P, const LayerRT& l, int batch, 
         if (want(li)) {
             PrefetchArgs pf;   // none when a launch is timed by itself
             if (only < 0)
-                pf = prefetch_args(P, &l - P->L.data(), batch, p.cfg,
+                pf = prefetch_args(P, &l - P->L.data(), batch,
                                    p.tiles_m * p.tiles_co * p.splits);
             if (hook) hook->before(l, li, s);
             e = is_split_cfg(p.cfg)
@@ -810,9 +826,8 @@ hipError_t enqueue_all(const ppipe_partition* P, int batch, const void* in, void
                                               buf_ptr(P, m.res_buf, in, out),
                                               const_cast<void*>(buf_ptr(P, m.out_buf, in, out)),
                                               false, W);
-            const int own = a0.tiles_m * a0.tiles_co + a1.tiles_m * a1.tiles_co;
             e = launch_conv_gemm_pair(P->dtype, l.plans[batch - 1].cfg, a0, a1,
-                                      prefetch_args(P, i, batch, l.plans[batch - 1].cfg, own), s);
+                                      prefetch_args(P, i, batch, launch_blocks(P, l, batch)), s);
         } else {
             e = enqueue_layer(P, l, batch, in, out, s, hook, -1, &W);
         }
@@ -2093,8 +2108,13 @@ int ppipe_layer_info(const ppipe_partition* h, int32_t index, int32_t batch,
         const Plan& p = l.plans[batch - 1];
         k += " tiles=" + std::to_string(p.tiles_m * p.tiles_co) + " splits=" +
              std::to_string(p.splits);
-        if (l.pair >= 0 && pair_runs(h, l.pair_lead ? l : h->L[l.pair],
-                                     l.pair_lead ? h->L[l.pair] : l, batch))
+        const bool paired = l.pair >= 0 && pair_runs(h, l.pair_lead ? l : h->L[l.pair],
+                                                     l.pair_lead ? h->L[l.pair] : l, batch);
+        size_t ahead = 0;
+        if (!fuse_runs(h, l, batch, false) && !(paired && !l.pair_lead) &&
+            prefetch_args(h, &l - h->L.data(), batch, launch_blocks(h, l, batch), &ahead).blocks)
+            k += " ahead=" + std::to_string(h->L[ahead].index);
+        if (paired)
             k += " paired=" + std::to_string(h->L[l.pair].index);
         info->forced = p.forced ? 1 : 0;
     }
