@@ -114,33 +114,34 @@ fused_block_kernel(FusedBlockArgs a)
     const auto wesrc = make_rsrc(a.we, (uint32_t)a.Ce * a.Kpe * 2);
     const auto wpsrc = make_rsrc(a.wp, (uint32_t)a.Co * a.Kpp * 2);
     uint4 ae[2], ap[CFO];
+    // A row past the last lies past the buffer (c0 + 8 q < Kpp, 8 q < Kpe), where
+    // the range check gives zeros.  Row tests and masks kept here as scalar pairs
+    // made the loop spill scalar registers (64 output channels at stride 2: 123
+    // moves to and from lanes per chunk).
+    const uint32_t e_off = (uint32_t)(r * a.Kpe + 8 * q) * 2u, p_off = (uint32_t)(r * a.Kpp + 8 * q) * 2u;
     auto load_e = [&](int c0) {
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            const int row = c0 + 16 * f + r;
-            ae[f] = buf_load16(wesrc, row < a.Ce ? (uint32_t)(row * a.Kpe + 8 * q) * 2u : OOB);
-        }
+        for (int f = 0; f < 2; ++f)
+            ae[f] = buf_load16(wesrc, e_off + (uint32_t)((c0 + 16 * f) * a.Kpe * 2));
     };
     auto load_p = [&](int c0) {
 #pragma unroll
-        for (int f = 0; f < CFO; ++f) {
-            const int row = 16 * f + r;
-            ap[f] = buf_load16(wpsrc, row < a.Co ? (uint32_t)(row * a.Kpp + c0 + 8 * q) * 2u : OOB);
-        }
+        for (int f = 0; f < CFO; ++f)
+            ap[f] = buf_load16(wpsrc, p_off + (uint32_t)((16 * f * a.Kpp + c0) * 2));
     };
     load_e(0);
 
     // ---- input pixels of the halo: groups wave, wave + 4, ... ----
     const auto xsrc = make_rsrc(a.x, (uint32_t)a.N * a.H * a.W * a.C * 2);
     uint4 xb[NF];
-    uint32_t inside = 0;     // bit f: the lane's pixel of group f is in the image
+    uint32_t inside[NF];     // ones where the lane's pixel of group f is in the image
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         const int p = (f * 4 + wave) * 16 + r;
         const int hr = p / HW, hc = p - hr * HW;
         const int ih = ih0 + hr, iw = iw0 + hc;
         const bool ok = p < hpx && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-        inside |= ok ? 1u << f : 0u;
+        inside[f] = ok ? 0xffffffffu : 0u;
         xb[f] = buf_load16(xsrc, ok && 8 * q < a.C
                                      ? (uint32_t)(((n * a.H + ih) * a.W + iw) * a.C + 8 * q) * 2u : OOB);
     }
@@ -160,6 +161,21 @@ fused_block_kernel(FusedBlockArgs a)
     const float elo = a.acte == ACT_NONE ? -INFINITY : 0.0f, ehi = a.acte == ACT_RELU6 ? 6.0f : INFINITY;
     const float dlo = a.actd == ACT_NONE ? -INFINITY : 0.0f, dhi = a.actd == ACT_RELU6 ? 6.0f : INFINITY;
 
+    // epilogue: lane's pixel 16 wave + r, channels 16 f + 4 q .. + 4; the addresses
+    // wait in vector registers (the loop needs the scalar ones)
+    T* yp = nullptr;
+    const T* rp = nullptr;
+    const float *scp = a.sp + 4 * q, *bip = a.bp + 4 * q;
+    {
+        const int p = wave * 16 + r, prow = p / a.TW, oh = oh0 + prow, ow = ow0 + p - prow * a.TW;
+        if (p < a.TH * a.TW && oh < a.Ho && ow < a.Wo) {
+            const size_t base = ((size_t)(n * a.Ho + oh) * a.Wo + ow) * a.Co + 4 * q;
+            yp = (T*)a.y + base;
+            rp = a.res ? (const T*)a.res + base : nullptr;
+        }
+    }
+    asm volatile("" : "+v"(yp), "+v"(rp));
+
     floatx4 acc[CFO];
 #pragma unroll
     for (int f = 0; f < CFO; ++f) acc[f] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -168,9 +184,10 @@ fused_block_kernel(FusedBlockArgs a)
     auto load_d = [&](int c0) {
         const int c = min(c0 + 8 * wave, a.Ce - 8);
 #pragma unroll
-        for (int k = 0; k < 9; ++k) dw[k] = uniform_load<uintx4>((const T*)a.wd + k * a.Ce + c);
-        dsc = uniform_load<floatx8>(a.sd + c);
-        dbi = uniform_load<floatx8>(a.bd + c);
+        for (int k = 0; k < 9; ++k)
+            dw[k] = uniform_load<uintx4>((const char*)a.wd + (uint32_t)((k * a.Ce + c) * 2));
+        dsc = uniform_load<floatx8>((const char*)a.sd + (uint32_t)(c * 4));
+        dbi = uniform_load<floatx8>((const char*)a.bd + (uint32_t)(c * 4));
     };
 
     auto expand = [&](int i) {
@@ -190,15 +207,14 @@ fused_block_kernel(FusedBlockArgs a)
             const float4 bi = *(const float4*)(s_bn + Cpad + i * FB_CH + 16 * h + 4 * q);
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                const bool in = (inside >> f) & 1u;
                 const floatx4 w = v[f][h];
                 uint2 u;
                 u.x = pack2<T>(clamp_act(w[0] * sc.x + bi.x, elo, ehi),
                                clamp_act(w[1] * sc.y + bi.y, elo, ehi));
                 u.y = pack2<T>(clamp_act(w[2] * sc.z + bi.z, elo, ehi),
                                clamp_act(w[3] * sc.w + bi.w, elo, ehi));
-                u.x = in ? u.x : 0u;
-                u.y = in ? u.y : 0u;
+                u.x &= inside[f];
+                u.y &= inside[f];
                 *(uint2*)(E + ((2 * h + (q >> 1)) * HALO + (f * 4 + wave) * 16 + r) * 16 + (q & 1) * 8) = u;
             }
         }
@@ -260,27 +276,24 @@ fused_block_kernel(FusedBlockArgs a)
     project(nch - 1);
 
     // ---- epilogue: lane holds four output channels of its pixel ----
-    const float plo = a.actp == ACT_NONE ? -INFINITY : 0.0f, phi = a.actp == ACT_RELU6 ? 6.0f : INFINITY;
-    const int p = wave * 16 + r;
-    const int prow = p / a.TW, oh = oh0 + prow, ow = ow0 + p - prow * a.TW;
-    if (p >= a.TH * a.TW || oh >= a.Ho || ow >= a.Wo)
+    if (!yp)
         return;
-    const size_t base = ((size_t)(n * a.Ho + oh) * a.Wo + ow) * a.Co;
+    const float plo = a.actp == ACT_NONE ? -INFINITY : 0.0f, phi = a.actp == ACT_RELU6 ? 6.0f : INFINITY;
 #pragma unroll
     for (int f = 0; f < CFO; ++f) {
         const int co = 16 * f + 4 * q;
         if (co >= a.Co)
             continue;
-        const float4 s4 = *(const float4*)(a.sp + co), b4 = *(const float4*)(a.bp + co);
+        const float4 s4 = *(const float4*)(scp + 16 * f), b4 = *(const float4*)(bip + 16 * f);
         float4 v = make_float4(acc[f][0] * s4.x + b4.x, acc[f][1] * s4.y + b4.y,
                                acc[f][2] * s4.z + b4.z, acc[f][3] * s4.w + b4.w);
-        if (a.res) {
-            const float4 z = Vec4<T>::load((const T*)a.res + base + co);
+        if (rp) {
+            const float4 z = Vec4<T>::load(rp + 16 * f);
             v.x += z.x; v.y += z.y; v.z += z.z; v.w += z.w;
         }
         v.x = clamp_act(v.x, plo, phi); v.y = clamp_act(v.y, plo, phi);
         v.z = clamp_act(v.z, plo, phi); v.w = clamp_act(v.w, plo, phi);
-        Vec4<T>::store((T*)a.y + base + co, v);
+        Vec4<T>::store(yp + 16 * f, v);
     }
 }
 
