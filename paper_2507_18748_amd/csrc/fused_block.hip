@@ -22,9 +22,10 @@
 // every sum runs in the same order, so the output has the same bits.
 //
 // What bounds it: instruction issue (a lone wave of a SIMD issues a vector
-// instruction every 8 to 10 cycles, two waves fill it), about 2 us per chunk
+// instruction every 8 to 10 cycles, two waves fill it), about 1 us per chunk
 // for a lone block.  Measured as a whole (MobileNetV2 [0, 39), bf16, one graph
-// replay, layers -> blocks): batch 5 190 -> 157 us, 32 321 -> 251, 64 490 -> 358.
+// replay, layers -> blocks): batch 1 146 -> 139 us, 5 182 -> 144, 32 313 -> 237,
+// 64 476 -> 342.
 #include "gemm_device.h"
 
 #include <algorithm>

@@ -407,15 +407,27 @@ Plan choose_plan(int M, int Co, int K, int dt, bool skinny_ok, bool pw_ok, bool 
     return p;
 }
 
-// Plan of an inverted-residual block as one launch: always for the shapes the
-// kernel takes, but for blocks of more than 144 expanded channels (six chunks
-// in a row) only from 48 tiles on, where the launches it replaces take longer
-// (MobileNetV2 [0, 39) with and without them: batch 1 146.9 -> 148.4 us, 3
-// 150.4 -> 150.7, 5 154.9 -> 153.1, 10 182 -> 177, 32 282 -> 251).  Blocks of
-// 64 and more input channels gain nothing (14x14 maps, 384 channels, batch 32:
-// 20.0 us as three launches, 24.9 as one), and neither does a depthwise layer
-// and its projection alone (32 channels at 112x112, batch 32: 321 -> 325 us).
-FusePlan choose_fuse(const LayerRT& dw, int batch, const ppipe_tuning& tune, int cus)
+// Plan of an inverted-residual block as one launch.  Both sides measured at 4800
+// random blocks within the kernel's limits (bf16, 7x7 to 240x240 maps, batch 1 to
+// 64, a graph replay of four):
+//  * A lone block takes about 2.7 us and 0.93 us per 32 expanded channels at
+//    stride 1, 1.22 at stride 2, against 8 to 10 us for the three launches on
+//    maps below 16384 pixels: 0.5 to 0.95 of them, except long chains at stride
+//    2: six chunks 1.05-1.24 below 8000 input pixels and 0.83-1.05 from there on,
+//    five with more than 32 output channels 0.96-1.10 below 4000.
+//  * On large grids a tile costs the same however few of its chunk's channels
+//    there are, and the three launches stream maps that fit the memory-side
+//    cache: from 24 tiles per CU blocks of at most 16 expanded channels take
+//    1.05-1.9 times as long (8 -> 8 channels at 224x224, batch 64: 145 against 75
+//    us), those of 24 with more than 16 outputs 0.95-1.14, and at stride 1 those of at most 72 with more than 48 output channels,
+//    maps of up to 350 MB in all, 1.02-1.2 times (32 -> 64 at 112x112, batch 64:
+//    70 against 61 us).
+// Of 2600 further random blocks seven are above 1.02 with these lines, the worst at
+// 1.10, the median of those in one launch at 0.54.  Blocks of 64 and more input channels gain nothing (14x14 maps, 384 channels, batch 32: 20.0
+// us as three launches, 24.9 as one), and neither does a depthwise layer and its
+// projection alone (32 channels at 112x112, batch 32: 321 -> 325 us).
+FusePlan choose_fuse(const LayerRT& l, const LayerRT& dw, const LayerRT& pr, int batch,
+                     const ppipe_tuning& tune, int cus)
 {
     FusePlan f;
     if (tune.no_pair || tune.gemm_cfg >= 0 || tune.no_pointwise || tune.stream_grid ||
@@ -424,7 +436,15 @@ FusePlan choose_fuse(const LayerRT& dw, int batch, const ppipe_tuning& tune, int
     fused_block_tile(dw.Ho, dw.Wo, dw.stride, &f.TH, &f.TW);
     f.tiles_h = (dw.Ho + f.TH - 1) / f.TH;
     f.tiles_w = (dw.Wo + f.TW - 1) / f.TW;
-    f.on = dw.C <= 144 || (int64_t)batch * f.tiles_h * f.tiles_w * 256 >= (int64_t)48 * cus;
+    auto at_least = [&](int64_t v, int64_t n256) { return v * 256 >= n256 * cus; };
+    const int64_t in = (int64_t)batch * dw.H * dw.W, out = (int64_t)batch * dw.Ho * dw.Wo;
+    const int chunks = (dw.C + 31) / 32;
+    const bool large = at_least((int64_t)batch * f.tiles_h * f.tiles_w, 24 * 256);
+    const double map_mb = 2e-6 * ((double)in * (l.C + dw.C) + (double)out * (dw.C + pr.Co));
+    f.on = !(dw.stride == 2 && chunks >= 6 && !at_least(in, 8000)) &&
+           !(dw.stride == 2 && chunks == 5 && pr.Co > 32 && !at_least(in, 4000)) &&
+           !(large && (dw.C <= 16 || (dw.C <= 24 && pr.Co > 16))) &&
+           !(large && dw.stride == 1 && dw.C <= 72 && pr.Co > 48 && map_mb <= 350);
     return f;
 }
 
@@ -1271,7 +1291,7 @@ int build(ppipe_partition* P, const ppipe_model_desc* d, int begin, int end, int
         l.fuse_plans.resize(P->max_batch);
         const LayerRT& dw = P->L[i + 1 - begin];
         for (int b = 1; b <= P->max_batch; ++b)
-            l.fuse_plans[b - 1] = choose_fuse(dw, b, P->tune, P->cus);
+            l.fuse_plans[b - 1] = choose_fuse(l, dw, (&dw)[1], b, P->tune, P->cus);
     }
     P->ws_bytes = ws;
     // layers that a split kernel runs at some batch: the bounds of their sums,

@@ -149,3 +149,37 @@ def test_timed_runs_issue_the_served_launches():
         recs = part.timing_read()
         assert [r["layer"] for r in recs] == [0, 1, 2] and all(r["mean_us"] > 0 for r in recs)
         assert not any("fused" in r["kernel"] for r in recs)
+
+
+# (C, Ce, Co, stride, side, batch, one launch): both sides of every line of the
+# dispatch rule
+RULE = [
+    (24, 192, 24, 1, 14, 1, True),        # stride 1: any length
+    (24, 160, 24, 2, 14, 1, True),        # stride 2: five chunks, few outputs
+    (24, 128, 64, 2, 14, 1, True),
+    (24, 136, 64, 2, 14, 1, False),       # five chunks and more than 32 outputs: from 4000 pixels
+    (24, 136, 64, 2, 64, 1, True),
+    (24, 168, 24, 2, 40, 4, False),       # six chunks: from 8000
+    (24, 168, 24, 2, 40, 5, True),
+    (8, 16, 16, 1, 112, 31, True),        # few expanded channels: below 24 tiles per CU
+    (8, 16, 16, 1, 112, 32, False),
+    (8, 24, 16, 1, 112, 32, True),
+    (8, 24, 20, 1, 112, 32, False),
+    (8, 32, 20, 1, 112, 32, True),
+    (8, 72, 48, 1, 112, 32, True),
+    (8, 72, 52, 1, 112, 32, False),       # many outputs of few channels, maps within 350 MB
+    (8, 80, 52, 1, 112, 32, True),
+    (8, 72, 52, 1, 112, 64, False),
+    (16, 72, 52, 1, 128, 64, True),
+]
+
+
+@pytest.mark.parametrize("c,ce,co,s,side,batch,on", RULE)
+def test_dispatch_rule(c, ce, co, s, side, batch, on):
+    from paper_2507_18748_amd import Partition
+    m = make((c, side, side), block(c, ce, co, s, 1, False, ("relu6", "relu6", "none"))[1:4])
+    for i, L in enumerate(m.layers):
+        L.src = i - 1
+    with Partition(m.layers, W.model_params(m, 0, "bf16"), (c, side, side), 0, 3, "bf16",
+                   max_batch=batch) as part:
+        assert ("fused=0-2" in part.layer_info(0, batch)["kernel"]) == on
