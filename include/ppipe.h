@@ -98,7 +98,9 @@ typedef struct {
     int32_t out_c, out_h, out_w;     /* per-image output of the range */
     int32_t out_dtype;               /* PPIPE_F32 when the range ends with FC_SOFTMAX */
     int64_t in_bytes_per_image, out_bytes_per_image;
-    int64_t weight_bytes;            /* device bytes of packed weights, scales and biases */
+    int64_t weight_bytes;            /* device bytes of packed weights, scales and biases; an
+                                        fp32 layer that the split kernels run at some batch
+                                        holds 10 bytes a weight (4 and its three planes) */
     int64_t workspace_bytes;         /* device bytes of activation and split-K buffers */
     int32_t tuned;                   /* 1 when created with a planner override
                                         (ppipe_partition_create_tuned), else 0 */
@@ -140,7 +142,10 @@ typedef struct {
  * Validates the range and every layer shape, folds batch norm into fp32
  * per-channel scale and bias, repacks weights to the kernels' layout in
  * dtype, and allocates device weights plus activation and split-K buffers
- * sized for desc->max_batch.  Returns NULL on error (PPIPE_E_SPLIT when a
+ * sized for desc->max_batch.  Sums are in fp32.  PPIPE_F32 layers with sums of
+ * 256 and more terms run on bf16 matrix instructions with every operand split
+ * into three bf16 values that hold it exactly; what is left out of a product
+ * stays below 2^-24 of it.  Returns NULL on error (PPIPE_E_SPLIT when a
  * layer in the range reads a tensor produced before layer_begin other than
  * layer_begin-1's output, or a layer after the range reads one produced
  * inside it other than layer_end-1's output).  Uses the current HIP device. */

@@ -14,7 +14,8 @@
 //    each lane of a 16x16 accumulator holds 4 consecutive channels of one
 //    pixel: the NHWC epilogue stores 8 bytes (16-bit types) per lane.
 //  * 16-bit types use v_mfma_f32_16x16x32_{f16,bf16}; fp32 uses
-//    v_mfma_f32_16x16x4_f32 (full fp32 products, no reduced-precision path).
+//    v_mfma_f32_16x16x4_f32 here (fp32 layers with longer sums and more pixels
+//    run on bf16 instructions, split_gemm.hip).
 //  * A stage is BM x BK weights plus BN x BK activations (BK = 128 bytes of
 //    K per row), staged through LDS (rows padded by 16 bytes) with two LDS
 //    buffers.  Global loads run DEPTH stages ahead in a ring of register sets

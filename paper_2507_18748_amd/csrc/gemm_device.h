@@ -73,14 +73,6 @@ template <typename T> struct Vec4 {   // 16-bit types
     }
 };
 
-// c ? v : 0 per component.  A conditional expression on uint4 (a class type)
-// is lowered as a select between two addresses, which forces both operands
-// into scratch memory; scalar selects keep everything in registers.
-__device__ __forceinline__ uint4 keep_if(bool c, const uint4& v)
-{
-    return make_uint4(c ? v.x : 0u, c ? v.y : 0u, c ? v.z : 0u, c ? v.w : 0u);
-}
-
 // Compile-time loop: f(std::integral_constant<int, I>) for I in [B, E).  Keeps
 // register-ring indices constant so the ring never lands in scratch memory.
 template <int B, int E, typename F>

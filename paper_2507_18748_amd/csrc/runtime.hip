@@ -203,7 +203,7 @@ namespace {
 // Kernel plan of a GEMM-shaped layer at one batch: kernel family, tile
 // shape, waves per tile (skinny) and tile order.  Deterministic in (M, Co, K,
 // dtype, eligibility) so that the latency table, the benchmark and the
-// parity tests exercise the same launches.
+// parity tests exercise the same launches (timed runs keep paired layers apart).
 Plan choose_plan(int M, int Co, int K, int dt, bool skinny_ok, bool pw_ok, bool stem_ok,
                  bool split_ok, bool split_free, const ppipe_tuning& tune, int cus)
 {
@@ -248,7 +248,9 @@ Plan choose_plan(int M, int Co, int K, int dt, bool skinny_ok, bool pw_ok, bool 
     //    most 64 output channels with at least 512 such tiles (fewer operand
     //    bytes per FLOP: VGG-16 conv1_2 at batch 16 124 -> 108 us, ResNet-152's
     //    7x7 stem at batch 64 116 -> 93 us);
-    //  * small fp32 layers take the skinny kernel (no reduction pass); so do
+    //  * fp32 layers of at most 32 pixels with K >= 256 take the skinny kernel
+    //    (no reduction pass), and up to 4096 pixels those that the split kernels
+    //    below cannot take (channels not a multiple of 32 in a window); so do
     //    16-bit layers with a long K loop (>= 1024) whose 16x16 skinny grid
     //    holds at least 128 pixels and fits one block per CU: ResNet-152's
     //    196-pixel layer3 convolutions at batch 1, where 64x64 tiles leave 16
