@@ -142,9 +142,9 @@ typedef struct {
  * Validates the range and every layer shape, folds batch norm into fp32
  * per-channel scale and bias, repacks weights to the kernels' layout in
  * dtype, and allocates device weights plus activation and split-K buffers
- * sized for desc->max_batch.  Sums are in fp32.  PPIPE_F32 layers with sums of
- * 256 and more terms run on bf16 matrix instructions with every operand split
- * into three bf16 values that hold it exactly; what is left out of a product
+ * sized for desc->max_batch.  Sums are in fp32.  Most PPIPE_F32 layers with
+ * sums of 256 and more terms and more than 32 output pixels run on bf16 matrix
+ * instructions with every operand split into three bf16 values that hold it; what is left out of a product
  * stays below 2^-24 of it.  Returns NULL on error (PPIPE_E_SPLIT when a
  * layer in the range reads a tensor produced before layer_begin other than
  * layer_begin-1's output, or a layer after the range reads one produced
