@@ -183,3 +183,27 @@ def test_dispatch_rule(c, ce, co, s, side, batch, on):
     with Partition(m.layers, W.model_params(m, 0, "bf16"), (c, side, side), 0, 3, "bf16",
                    max_batch=batch) as part:
         assert ("fused=0-2" in part.layer_info(0, batch)["kernel"]) == on
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("acts", [("relu6", "relu6", "none"), ("none", "none", "none")])
+@pytest.mark.parametrize("ce,s", [(72, 1), (40, 2)])      # part-filled last chunks
+def test_non_finite_inputs(dtype, acts, ce, s):
+    """Infinities, NaN and the type's largest values in the input and the residual:
+    the bits of the separate launches, and pixels out of their reach stay finite."""
+    from paper_2507_18748_amd import Partition
+    n, c, h, w = 2, 24, 13, 19
+    m = make((c, h, w), block(c, ce, c, s, 1, s == 1, acts))
+    P = W.model_params(m, 0, dtype)
+    x = W.partition_input((c, h, w), n, 0, dtype, "normal")
+    big = 65504.0 if dtype == "f16" else 3.38e38
+    x[0, 0, 0, 0], x[0, 5, 6, 7], x[0, 23, 12, 18] = np.inf, -np.inf, np.nan
+    x[1, 3, 4, 4], x[1, 4, 4, 5], x[1, 9, 12, 0] = big, -big, np.inf
+    outs = []
+    for tuning in (None, {"no_pair": 1}):
+        with Partition(m.layers, P, (c, h, w), 0, 5, dtype, max_batch=n, tuning=tuning) as part:
+            assert ("fused=1-3" in part.layer_info(1, n)["kernel"]) == (tuning is None)
+            outs.append(gpu_forward(part, x))
+    assert np.isfinite(outs[1][:, :, 2 // s, 12 // s]).all()
+    assert acts[0] == "relu6" or not np.isfinite(outs[1]).all()   # (relu6 bounds every value)
+    np.testing.assert_array_equal(outs[0], outs[1])
